@@ -183,6 +183,20 @@ def work(case):
     return {"bytes": total, "flops": flops}
 
 
+def exact(case, seed):
+    """The products in float64 on the weights and activations that `prepare` draws from this seed."""
+    if case["op"] in ("decompress", "encode"):
+        return None  # bytes
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    step = case["op"] == "decode_step"
+    out = []
+    for n, k in [LAYERS_8B[name] for name in STEP_LAYERS] if step else [(case["N"], case["K"])]:
+        w = _weights(n, k, case["law"], gen)
+        a = torch.randn(case["M"], k, generator=gen, device="cuda", dtype=torch.float32).to(torch.bfloat16)
+        out.append(a.double() @ w.double().t())
+    return out if step else out[0]
+
+
 def tolerance(case):
     """Measured against the products in float64 over the listed cases and drawn ones: FP32 results
     differ by at most 6.5e-7 (largest element 1e-5 of the RMS), BF16 results from the rounded
