@@ -98,8 +98,8 @@ int zs_encode(const uint16_t *W_host, int64_t N, int64_t K, int64_t ldw,
  *   blob_dev  256-byte aligned, at least zs_encode_bound(N, K) bytes or ZS_ERR_SIZE  (device, out)
  *   out       descriptor                                                             (host, out)
  *   workspace_dev  ZS_ENCODE_WORKSPACE_BYTES of scratch, 16-byte aligned, any contents (device)
- * Runs five small kernels on hip_stream and waits for the stream twice (the exponent histogram
- * and the section sizes are read back by the host): not for use under graph capture.  Bytes of
+ * Runs five kernels on hip_stream and waits for the stream once (the host reads the section
+ * sizes back for the descriptor): not for use under graph capture.  Bytes of
  * blob_dev beyond out->total_bytes are left as they were. */
 #define ZS_ENCODE_WORKSPACE_BYTES ((size_t)4096)
 int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int64_t ldw, void *blob_dev,

@@ -1,34 +1,42 @@
 // GPU-side TCA-TBE packer (Algorithm 1 and Section 4.2 of the ZipServ paper): the same blob,
 // byte for byte, as the host packer zs_encode, from a matrix that already lies in device memory.
 //
-//   1. hist_kernel    exponent histogram                         -> host picks the window
-//   2. count_kernel   in-window elements of every BlockTile      (parked in the offset section)
-//   3. scan_kernel    segment offsets = prefix sums of the padded segment sizes, totals
-//   4. pack_kernel    one wave per BlockTile: bit-planes, H bytes, L halfwords at their final
-//                     place; fill_kernel zeroes the gaps between sections
-// The host reads 2 KB after step 1 and 64 bytes after step 3 (two stream synchronisations): the
-// window decides what is counted, the totals decide where the L section starts.
+//   1. sample_kernel  predicts the exponent window from 16 K of the weights
+//   2. hist_kernel    exponent histogram of all weights, and the in-window elements of every
+//                     BlockTile under the predicted window (parked in the offset section)
+//   3. recount_kernel repeats the counts when the window of the full histogram is another one
+//                     (near ties only); otherwise it ends at once
+//   4. scan_kernel    segment offsets = prefix sums of the padded segment sizes, totals
+//   5. pack_kernel    one wave per BlockTile: bit-planes, H bytes, L halfwords, assembled in LDS;
+//                     one more workgroup zeroes the gaps between the sections
+// The matrix is read twice.  Window, offsets and the start of the L section stay on the device;
+// the host waits once, at the end, for the totals that fill the descriptor.
 // Every store is checked against the caller's capacity, whatever the counts say.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
 
 #include "zipserv.h"
+#include "zs_device.h"
 #include "zs_format.h"
+
+using namespace zs;
 
 namespace {
 
-typedef uint32_t __attribute__((ext_vector_type(4))) u32x4;
+typedef uint16_t __attribute__((ext_vector_type(2))) u16x2;
 
 constexpr int kHistWords = 256;                         // uint64 bins at the start of the workspace
 constexpr size_t kTotalsAt = kHistWords * 8;            // then: struct Totals
 struct Totals {
     uint64_t h_units, l_units, n_high;
     uint32_t max_h, max_l;
+    uint32_t win_lo;       // first exponent of the window (Algorithm 1, phase I)
+    uint32_t predicted_lo; // the window the parked counts were taken with
 };
 static_assert(kTotalsAt + sizeof(Totals) <= ZS_ENCODE_WORKSPACE_BYTES, "workspace layout");
 
-inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+__host__ __device__ inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
 // The eight weights of FragTile row `lane` of TensorCoreTile tt of a BlockTile (the lane order of
 // Section 4.2: lane l <-> FragTile l / 8, row l % 8), as 16 bytes.
@@ -38,161 +46,367 @@ __device__ __forceinline__ u32x4 load_row(const uint16_t *tile, int64_t ldw, int
     const uint32_t row = 16 * (tt & 3) + 8 * (ft & 1u) + r, col = 32 * (tt >> 2) + 8 * (ft >> 1);
     return *reinterpret_cast<const u32x4 *>(tile + (int64_t)row * ldw + col);
 }
-__device__ __forceinline__ uint32_t element(const u32x4 &v, int c)
+__device__ __forceinline__ const uint16_t *tile_at(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t bt)
 {
-    const uint32_t w = c < 2 ? v.x : c < 4 ? v.y : c < 6 ? v.z : v.w;
-    return (c & 1) ? (w >> 16) : (w & 0xFFFFu);
-}
-__device__ __forceinline__ bool in_window(uint32_t w, uint32_t win_lo) { return ((w >> 7) & 0xFFu) - win_lo < 7u; }
-
-// One workgroup of 256 threads per BlockTile; each thread sees 16 elements.
-__global__ __launch_bounds__(256) void hist_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, unsigned long long *hist)
-{
-    __shared__ uint32_t bins[256];
-    bins[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t bt = blockIdx.x, strip = bt / k_blocks, kb = bt % k_blocks;
-    const uint16_t *tile = W + (int64_t)strip * 64 * ldw + (int64_t)kb * 64;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    for (int t = 0; t < 2; ++t) {
-        const u32x4 v = load_row(tile, ldw, 2 * wave + t, lane);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) atomicAdd(&bins[(element(v, c) >> 7) & 0xFFu], 1u);
-    }
-    __syncthreads();
-    if (bins[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)bins[threadIdx.x]);
+    return W + (int64_t)(bt / k_blocks) * 64 * ldw + (int64_t)(bt % k_blocks) * 64;
 }
 
-// In-window elements per BlockTile, written to the first word of the BlockTile's offset pair.
-__global__ __launch_bounds__(256) void count_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t win_lo,
-                                                    uint32_t *offsets)
+// Codewords of two weights, one per halfword: exponent - (lo - 1) = 1..7 inside the window, 8
+// outside it (low three bits zero, as the format wants them, and bit 3 marks the fallback).
+__device__ __forceinline__ uint32_t codes_of(uint32_t pair, uint32_t lo2)
 {
-    __shared__ uint32_t total;
-    if (threadIdx.x == 0) total = 0;
-    __syncthreads();
-    const uint32_t bt = blockIdx.x, strip = bt / k_blocks, kb = bt % k_blocks;
-    const uint16_t *tile = W + (int64_t)strip * 64 * ldw + (int64_t)kb * 64;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    uint32_t c_in = 0;
-    for (int t = 0; t < 2; ++t) {
-        const u32x4 v = load_row(tile, ldw, 2 * wave + t, lane);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) c_in += in_window(element(v, c), win_lo) ? 1u : 0u;
+    const u16x2 e = __builtin_bit_cast(u16x2, (pair >> 7) & 0x00FF00FFu);
+    const u16x2 d = e - __builtin_bit_cast(u16x2, lo2);
+    const u16x2 c = __builtin_elementwise_min(d, u16x2{7, 7}) + u16x2{1, 1};
+    return __builtin_bit_cast(uint32_t, c);
+}
+
+// Bits 0, 4, ..., 28 of x (one per weight: even ones in the low half, odd ones in the high half) as
+// a byte in element order.
+__device__ __forceinline__ uint32_t gather_bits(uint32_t x)
+{
+    x &= 0x11111111u;
+    x |= x >> 15;                   // e1 -> 1, e3 -> 5, e5 -> 9, e7 -> 13
+    x = (x | (x >> 2)) & 0x0F0Fu;   // e0..e3 -> 0..3, e4..e7 -> 8..11
+    return (x | (x >> 4)) & 0xFFu;
+}
+
+// The window of maximal coverage, smallest start on ties; every thread of a workgroup of at least
+// 256 takes part and gets the result.  sums: 256 words of LDS for the reduction.
+struct Window {
+    uint32_t lo;
+    uint64_t covered;
+};
+__device__ inline Window pick_window(const unsigned long long *bins, unsigned long long *sums)
+{
+    const uint32_t t = threadIdx.x;
+    if (t < 256) {
+        unsigned long long s = 0;
+        if (t + ZS_WINDOW <= 256)
+            for (int j = 0; j < ZS_WINDOW; ++j) s += bins[t + j];
+        // one key: coverage first (below 2^56: N K < 2^35), then the smaller start
+        sums[t] = t + ZS_WINDOW <= 256 ? (s << 8) | (255u - t) : 0ull;
     }
-    atomicAdd(&total, c_in);
     __syncthreads();
-    if (threadIdx.x == 0) offsets[2 * (size_t)bt] = total;
+    for (uint32_t d = 128; d > 0; d >>= 1) {
+        if (t < d && sums[t + d] > sums[t]) sums[t] = sums[t + d];
+        __syncthreads();
+    }
+    const unsigned long long best = sums[0];
+    __syncthreads();
+    return Window{255u - (uint32_t)(best & 255u), best >> 8};
+}
+
+// Exponent histogram in LDS, 32 copies of each bin side by side: a lane adds to copy lane % 32, so
+// that the few exponents that hold most of the weights are spread over the banks (with one copy
+// the 64 lanes of a wave pile up on a handful of addresses).  A bin's copies take 128 bytes, so
+// that bits 14..7 of a weight are the byte offset of its bin as they stand.
+constexpr uint32_t kCopies = 32;
+__device__ __forceinline__ void count_pair(uint8_t *bins, uint32_t pair, uint32_t copy4)
+{
+    __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(bins + ((pair & 0x7F80u) | copy4)), 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(bins + (((pair >> 16) & 0x7F80u) | copy4)), 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t bin_total(const uint8_t *bins, uint32_t bin)
+{
+    uint32_t s = 0;
+    for (uint32_t j = 0; j < kCopies; ++j) s += reinterpret_cast<const uint32_t *>(bins)[bin * kCopies + ((bin + j) & (kCopies - 1))];
+    return s;
+}
+
+// One workgroup: clears the workspace and predicts the window from kSampleUnits 16-byte units of
+// the matrix, spread over it by a multiplicative sequence (no row or column stride is favoured).
+// The prediction is only that: the counts taken with it are used if the full histogram agrees.
+// Bound by the latency of scattered reads from one compute unit: 8192 units took 21.9 us, 2048 take
+// 7.7 us, and 16 K weights still place the window of the test laws (neighbouring windows of N(0, s)
+// weights differ by 1.7 % of coverage, sixteen standard deviations of the sample).
+constexpr uint32_t kSampleUnits = 2048;
+__global__ __launch_bounds__(1024) void sample_kernel(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, unsigned long long *hist,
+                                                      Totals *totals)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t bins[256 * kCopies * 4];
+    __shared__ unsigned long long sums[256], all[256];
+    const uint32_t t = threadIdx.x;
+    for (uint32_t i = t; i < 256 * kCopies; i += 1024) reinterpret_cast<uint32_t *>(bins)[i] = 0;
+    if (t < 256) hist[t] = 0;
+    __syncthreads();
+    const uint32_t row_units = (uint32_t)(K / 8);
+    const uint64_t units = (uint64_t)N * row_units;
+    u32x4 v[kSampleUnits / 1024];
+#pragma unroll
+    for (uint32_t i = 0; i < kSampleUnits / 1024; ++i) {
+        const uint32_t h = (i * 1024 + t) * 0x9E3779B1u; // a permutation of 32-bit numbers
+        const uint32_t u = (uint32_t)((uint64_t)h * units >> 32); // units < 2^32 (checked by the host)
+        v[i] = *reinterpret_cast<const u32x4 *>(W + (int64_t)(u / row_units) * ldw + (int64_t)(u % row_units) * 8);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kSampleUnits / 1024; ++i)
+        for (int c = 0; c < 4; ++c) count_pair(bins, v[i][c], (t & (kCopies - 1)) * 4);
+    __syncthreads();
+    if (t < 256) all[t] = bin_total(bins, t);
+    __syncthreads();
+    const Window w = pick_window(all, sums);
+    if (t == 0) totals->predicted_lo = w.lo;
+}
+
+// In-window elements of a BlockTile, per wave (all lanes get the sum of the fallbacks).
+__device__ __forceinline__ uint32_t fallbacks_of(const u32x4 (&v)[ZS_TT_PER_BT], uint32_t lo2)
+{
+    uint32_t f = 0; // two counters, one per halfword (a lane has 64 weights)
+#pragma unroll
+    for (int tt = 0; tt < ZS_TT_PER_BT; ++tt)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f += (codes_of(v[tt][c], lo2) >> 3) & 0x00010001u;
+    f = (f & 0xFFFFu) + (f >> 16);
+    return __builtin_amdgcn_readlane(wave_inclusive_scan(f), 63);
+}
+
+// Bound by the read of the matrix (235 MB of the 28672 x 4096 layer in 57 us, 4.1 TB/s; with one copy of
+// the bins, one BlockTile per workgroup and a separate counting pass it was 482 + 36 us).  A wave takes whole
+// BlockTiles, so their counts need no exchange between waves; two workgroups of 16 waves on a
+// compute unit keep 256 KB of loads in flight, and the global histogram gets one addition per
+// workgroup and bin in use.
+constexpr uint32_t kHistWaves = 16;
+__global__ __launch_bounds__(64 * kHistWaves) void hist_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
+                                                               unsigned long long *hist, const Totals *totals, uint32_t *offsets)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t bins[256 * kCopies * 4];
+    for (uint32_t i = threadIdx.x; i < 256 * kCopies; i += blockDim.x) reinterpret_cast<uint32_t *>(bins)[i] = 0;
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lo2 = totals->predicted_lo * 0x00010001u, copy4 = (lane & (kCopies - 1)) * 4;
+    for (uint64_t bt = (uint64_t)blockIdx.x * kHistWaves + wave; bt < n_bt; bt += (uint64_t)gridDim.x * kHistWaves) {
+        const uint16_t *tile = tile_at(W, ldw, k_blocks, (uint32_t)bt);
+        u32x4 v[ZS_TT_PER_BT];
+#pragma unroll
+        for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) v[tt] = load_row(tile, ldw, tt, lane);
+#pragma unroll
+        for (int tt = 0; tt < ZS_TT_PER_BT; ++tt)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) count_pair(bins, v[tt][c], copy4);
+        const uint32_t f = fallbacks_of(v, lo2);
+        if (lane == 0) offsets[2 * bt] = ZS_BT_ELEMS - f;
+    }
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        const uint32_t s = bin_total(bins, threadIdx.x);
+        if (s) atomicAdd(&hist[threadIdx.x], (unsigned long long)s);
+    }
+}
+
+// The counts again, under the window of the full histogram, when it is not the predicted one.
+__global__ __launch_bounds__(256) void recount_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
+                                                      const unsigned long long *hist, const Totals *totals, uint32_t *offsets)
+{
+    __shared__ unsigned long long sums[256];
+    const Window w = pick_window(hist, sums);
+    if (w.lo == totals->predicted_lo) return;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint64_t bt = (uint64_t)blockIdx.x * 4 + wave; bt < n_bt; bt += (uint64_t)gridDim.x * 4) {
+        const uint16_t *tile = tile_at(W, ldw, k_blocks, (uint32_t)bt);
+        u32x4 v[ZS_TT_PER_BT];
+#pragma unroll
+        for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) v[tt] = load_row(tile, ldw, tt, lane);
+        const uint32_t f = fallbacks_of(v, w.lo * 0x00010001u);
+        if (lane == 0) offsets[2 * bt] = ZS_BT_ELEMS - f;
+    }
 }
 
 // One workgroup: offsets[bt] = {sum of H units before bt, sum of L units before bt}, in place over
-// the counts left by count_kernel; offsets[n_bt] and the totals at the end.
-__global__ __launch_bounds__(1024) void scan_kernel(uint32_t *offsets, uint32_t n_bt, Totals *totals)
+// the parked counts; offsets[n_bt], the window and the totals at the end.  A thread takes eight
+// consecutive BlockTiles, so 8192 share one exchange between the waves (28672 BlockTiles: 16 us; one
+// BlockTile per thread and a scan through LDS took 140 us).  (Unit sums stay below
+// 2^32: the host refuses larger matrices.)
+__global__ __launch_bounds__(1024) void scan_kernel(uint32_t *offsets, uint32_t n_bt, const unsigned long long *hist, Totals *totals)
 {
-    __shared__ uint32_t sh[1024], sl[1024];
-    __shared__ uint64_t run_h, run_l, run_n;
-    __shared__ uint32_t max_h, max_l;
-    const uint32_t t = threadIdx.x;
-    if (t == 0) run_h = 0, run_l = 0, run_n = 0, max_h = 0, max_l = 0;
+    __shared__ unsigned long long sums[256];
+    __shared__ uint32_t wave_h[2][16], wave_l[2][16], max_h, max_l;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    if (t == 0) max_h = 0, max_l = 0;
+    uint32_t run_h = 0, run_l = 0, mh = 0, ml = 0, par = 0;
+    auto live_at = [&](uint64_t bt0) { return bt0 >= n_bt ? 0u : n_bt - bt0 < 8 ? (uint32_t)(n_bt - bt0) : 8u; };
+    u32x4 q[4]; // the counts of the round (even words)
+    auto fetch = [&](uint64_t bt0) {
+        if (live_at(bt0) == 8) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const u32x4 *>(offsets + 2 * bt0 + 4 * i);
+        } else {
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i) q[i / 2][2 * (i & 1)] = i < live_at(bt0) ? offsets[2 * (bt0 + i)] : 0u;
+        }
+    };
+    fetch(8 * t);
+    const Window w = pick_window(hist, sums);
+    for (uint64_t base = 0; base < n_bt; base += 8192, par ^= 1) {
+        const uint64_t bt0 = base + 8 * t;
+        const uint32_t live = live_at(bt0);
+        uint32_t hu[8], lu[8], h = 0, l = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+            const uint32_t nh = q[i / 2][2 * (i & 1)];
+            hu[i] = i < live ? (nh + 15u) / 16u : 0u, lu[i] = i < live ? (2u * (ZS_BT_ELEMS - nh) + 15u) / 16u : 0u;
+            h += hu[i], l += lu[i];
+            mh = max(mh, hu[i]), ml = max(ml, lu[i]);
+        }
+        fetch(bt0 + 8192); // in flight over the exchange between the waves
+        const uint32_t inc_h = wave_inclusive_scan(h), inc_l = wave_inclusive_scan(l);
+        if (lane == 63) wave_h[par][wave] = inc_h, wave_l[par][wave] = inc_l;
+        __syncthreads(); // (two sets of sums by turns: the next round writes the other one)
+        uint32_t at_h = run_h + inc_h - h, at_l = run_l + inc_l - l;
+        for (uint32_t i = 0; i < 16; ++i) {
+            const uint32_t sh = wave_h[par][i], sl = wave_l[par][i];
+            at_h += i < wave ? sh : 0u, at_l += i < wave ? sl : 0u;
+            run_h += sh, run_l += sl;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            u32x4 o;
+            o.x = at_h, o.y = at_l;
+            at_h += hu[2 * i], at_l += lu[2 * i];
+            o.z = at_h, o.w = at_l;
+            at_h += hu[2 * i + 1], at_l += lu[2 * i + 1];
+            if (live == 8) *reinterpret_cast<u32x4 *>(offsets + 2 * bt0 + 4 * i) = o;
+            else {
+                if (2 * i < (int)live) offsets[2 * (bt0 + 2 * i)] = o.x, offsets[2 * (bt0 + 2 * i) + 1] = o.y;
+                if (2 * i + 1 < (int)live) offsets[2 * (bt0 + 2 * i) + 2] = o.z, offsets[2 * (bt0 + 2 * i) + 3] = o.w;
+            }
+        }
+    }
     __syncthreads();
-    for (uint32_t base = 0; base < n_bt; base += 1024) {
-        const uint32_t bt = base + t;
-        const bool live = bt < n_bt;
-        const uint32_t nh = live ? offsets[2 * (size_t)bt] : 0u;
-        const uint32_t hu = live ? (nh + 15u) / 16u : 0u, lu = live ? (2u * (ZS_BT_ELEMS - nh) + 15u) / 16u : 0u;
-        sh[t] = hu, sl[t] = lu;
-        __syncthreads();
-        for (uint32_t d = 1; d < 1024; d <<= 1) { // inclusive scan of both arrays
-            const uint32_t ah = t >= d ? sh[t - d] : 0u, al = t >= d ? sl[t - d] : 0u;
-            __syncthreads();
-            sh[t] += ah, sl[t] += al;
-            __syncthreads();
-        }
-        if (live) {
-            offsets[2 * (size_t)bt] = (uint32_t)(run_h + sh[t] - hu);
-            offsets[2 * (size_t)bt + 1] = (uint32_t)(run_l + sl[t] - lu);
-            atomicMax(&max_h, hu);
-            atomicMax(&max_l, lu);
-            atomicAdd((unsigned long long *)&run_n, (unsigned long long)nh);
-        }
-        __syncthreads();
-        if (t == 0) run_h += sh[1023], run_l += sl[1023];
-        __syncthreads();
-    }
+    atomicMax(&max_h, mh);
+    atomicMax(&max_l, ml);
+    __syncthreads();
     if (t == 0) {
-        offsets[2 * (size_t)n_bt] = (uint32_t)run_h;
-        offsets[2 * (size_t)n_bt + 1] = (uint32_t)run_l;
-        totals->h_units = run_h, totals->l_units = run_l, totals->n_high = run_n;
-        totals->max_h = max_h, totals->max_l = max_l;
+        offsets[2 * (size_t)n_bt] = run_h;
+        offsets[2 * (size_t)n_bt + 1] = run_l;
+        totals->h_units = run_h, totals->l_units = run_l, totals->n_high = w.covered;
+        totals->max_h = max_h, totals->max_l = max_l, totals->win_lo = w.lo;
     }
-}
-
-__global__ void fill_kernel(uint8_t *p, uint64_t n)
-{
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) p[i] = 0;
-}
-
-// Exclusive prefix sum over the 64 lanes of a wave, and the wave total.
-__device__ __forceinline__ uint32_t wave_exclusive(uint32_t x, uint32_t lane, uint32_t &total)
-{
-    uint32_t inc = x;
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t up = __shfl_up(inc, d, 64);
-        if ((int)lane >= d) inc += up;
-    }
-    total = __shfl(inc, 63, 64);
-    return inc - x;
 }
 
 // One wave per BlockTile.  A lane owns one FragTile row per TensorCoreTile: its byte of each
 // bit-plane, its in-window bytes and its fallback halfwords, placed by prefix sums over the lanes.
+// Bound by memory (the matrix once, the blob once; 28672 x 4096: 75 us, 5.3 TB/s, a plain copy's rate;
+// with byte stores to global memory it was 148 us): everything is assembled in LDS and leaves in
+// 16-byte pieces.  The wave's buffer holds the bit-planes first and, once they are stored, the H
+// segment with the L segment behind it (together at most 8208 bytes whatever the mix), so four
+// workgroups fit on a compute unit.  A row's in-window bytes are compacted with two v_perm (selectors
+// from a table over the indicator byte), shifted to their byte position and combined with their
+// neighbours' by LDS OR; the buffer starts from zero, which also makes the segments' padding.
+constexpr uint32_t kPackBuf = 2 * ZS_BT_ELEMS + 32;
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
-                                                   uint32_t win_lo, uint8_t *blob, uint64_t cap, uint64_t off_bitmaps,
-                                                   const uint32_t *offsets, uint64_t off_H, uint64_t off_L)
+                                                   const Totals *totals, uint8_t *blob, uint64_t cap, const uint32_t *offsets,
+                                                   uint64_t off_offsets, uint64_t off_H)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t bt = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (bt >= n_bt) return;
-    const uint32_t strip = bt / k_blocks, kb = bt % k_blocks;
-    const uint16_t *tile = W + (int64_t)strip * 64 * ldw + (int64_t)kb * 64;
-    uint64_t h_at = off_H + (uint64_t)offsets[2 * (size_t)bt] * 16, l_at = off_L + (uint64_t)offsets[2 * (size_t)bt + 1] * 16;
-    const uint64_t h_end = off_H + (uint64_t)offsets[2 * (size_t)bt + 2] * 16, l_end = off_L + (uint64_t)offsets[2 * (size_t)bt + 3] * 16;
-    auto put8 = [&](uint64_t at, uint32_t v) {
-        if (at < cap) blob[at] = (uint8_t)v;
-    };
-    auto put16 = [&](uint64_t at, uint32_t v) {
-        if (at + 2 <= cap) *reinterpret_cast<uint16_t *>(blob + at) = (uint16_t)v;
-    };
-    for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) {
-        const u32x4 v = load_row(tile, ldw, tt, lane);
-        uint32_t b1 = 0, b2 = 0, b3 = 0, n_in = 0;
-        uint32_t hb[8], lw[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const uint32_t w = element(v, c), d = ((w >> 7) & 0xFFu) - win_lo;
-            const bool in = d < 7u;
-            const uint32_t code = in ? d + 1u : 0u; // exponent - base_exp, 1..7; 0 marks a fallback
-            b1 |= (code & 1u) << c, b2 |= ((code >> 1) & 1u) << c, b3 |= ((code >> 2) & 1u) << c;
-            hb[c] = ((w >> 8) & 0x80u) | (w & 0x7Fu);
-            lw[c] = w;
-            n_in += in ? 1u : 0u;
-        }
-        // byte r of a FragTile's 64-bit plane holds elements 8 r .. 8 r + 7: this lane's row
-        const uint64_t planes = off_bitmaps + (uint64_t)bt * ZS_BT_BITMAP_BYTES + (uint64_t)(tt * ZS_FT_PER_TT + (lane >> 3)) * ZS_FT_BITMAP_BYTES + (lane & 7u);
-        put8(planes, b1), put8(planes + 8, b2), put8(planes + 16, b3);
-        uint32_t h_total, l_total;
-        uint64_t h_pos = h_at + wave_exclusive(n_in, lane, h_total);
-        uint64_t l_pos = l_at + 2ull * wave_exclusive(8u - n_in, lane, l_total);
-        const uint32_t m = b1 | b2 | b3;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            if ((m >> c) & 1u) put8(h_pos++, hb[c]);
-            else put16(l_pos, lw[c]), l_pos += 2;
-        }
-        h_at += h_total, l_at += 2ull * l_total;
+    __shared__ __attribute__((aligned(16))) uint8_t bufs[4][kPackBuf];
+    __shared__ __attribute__((aligned(8))) u32x2 compact[256];
+    const uint64_t off_L = align_up(off_H + totals->h_units * 16, ZS_SECTION_ALIGN);
+    if (blockIdx.x == gridDim.x - 1) { // the gaps behind the four sections (each below 256 bytes)
+        const uint64_t end_L = off_L + totals->l_units * 16;
+        const uint64_t from[4] = {(uint64_t)n_bt * ZS_BT_BITMAP_BYTES, off_offsets + ((uint64_t)n_bt + 1) * 8,
+                                  off_H + totals->h_units * 16, end_L};
+        const uint64_t to[4] = {off_offsets, off_H, off_L, align_up(end_L, ZS_SECTION_ALIGN)};
+        for (int g = 0; g < 4; ++g)
+            if (from[g] + threadIdx.x < min(to[g], cap)) blob[from[g] + threadIdx.x] = 0;
+        return;
     }
-    // padding up to the 16-byte boundary where the next BlockTile's segments start
-    if (h_at + lane < h_end) put8(h_at + lane, 0);
-    if (l_at + lane < l_end) put8(l_at + lane, 0);
+    { // selectors that move the bytes of in-window elements to the front, zeros (0x0C) behind them
+        const uint32_t m = threadIdx.x;
+        uint64_t sel = 0x0C0C0C0C0C0C0C0Cull;
+        for (int e = 7; e >= 0; --e)
+            if ((m >> e) & 1u) sel = (sel << 8) | (uint32_t)e;
+        compact[m] = u32x2{(uint32_t)sel, (uint32_t)(sel >> 32)};
+    }
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t bt = blockIdx.x * 4 + wave;
+    if (bt >= n_bt) return;
+    const uint16_t *tile = tile_at(W, ldw, k_blocks, bt);
+    uint8_t *buf = bufs[wave];
+    u32x4 v[ZS_TT_PER_BT];
+#pragma unroll
+    for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) v[tt] = load_row(tile, ldw, tt, lane);
+    const uint32_t lo2 = totals->win_lo * 0x00010001u;
+
+    // ---- bit-planes: byte r of a FragTile's 64-bit plane holds elements 8 r .. 8 r + 7, this lane's row
+    uint32_t ind[ZS_TT_PER_BT]; // indicator bytes (1 = in-window element)
+#pragma unroll
+    for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) {
+        const uint32_t nib = codes_of(v[tt].x, lo2) | (codes_of(v[tt].y, lo2) << 4) | (codes_of(v[tt].z, lo2) << 8) |
+                             (codes_of(v[tt].w, lo2) << 12);
+        uint8_t *p = buf + (tt * ZS_FT_PER_TT + (lane >> 3)) * ZS_FT_BITMAP_BYTES + (lane & 7u);
+        p[0] = (uint8_t)gather_bits(nib), p[8] = (uint8_t)gather_bits(nib >> 1), p[16] = (uint8_t)gather_bits(nib >> 2);
+        ind[tt] = gather_bits(nib >> 3) ^ 0xFFu;
+    }
+    auto lds_done = []() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }; // lanes exchange through LDS
+    auto send = [&](uint64_t at, const uint8_t *from, uint32_t units, uint32_t max_units) {
+        for (uint32_t c = 0; c < max_units; c += 64) {
+            if (c >= units) break;
+            const uint32_t u = c + lane;
+            if (u < units && at + 16ull * u + 16 <= cap)
+                *reinterpret_cast<u32x4 *>(blob + at + 16ull * u) = *reinterpret_cast<const u32x4 *>(from + 16 * u);
+        }
+    };
+    lds_done();
+    send((uint64_t)bt * ZS_BT_BITMAP_BYTES, buf, ZS_BT_BITMAP_BYTES / 16, 96);
+
+    // ---- positions: in-window elements before the lane's row, three TensorCoreTiles to a prefix sum
+    uint32_t before[ZS_TT_PER_BT], nh = 0;
+#pragma unroll
+    for (int g = 0; g < ZS_TT_PER_BT; g += 3) {
+        uint32_t pk = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (g + i < ZS_TT_PER_BT) pk |= (uint32_t)__builtin_popcount(ind[g + i]) << (10 * i);
+        const uint32_t inc = wave_inclusive_scan(pk), exc = inc - pk, tot = __builtin_amdgcn_readlane(inc, 63);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (g + i < ZS_TT_PER_BT) {
+                before[g + i] = nh + ((exc >> (10 * i)) & 0x3FFu);
+                nh += (tot >> (10 * i)) & 0x3FFu;
+            }
+    }
+    const uint32_t h_units = (nh + 15u) / 16u, l_units = (2u * (ZS_BT_ELEMS - nh) + 15u) / 16u;
+    lds_done(); // the bit-planes have left the buffer
+    for (uint32_t u = lane; u < h_units + l_units; u += 64) *reinterpret_cast<u32x4 *>(buf + 16 * u) = u32x4{0u, 0u, 0u, 0u};
+    lds_done();
+
+    // ---- H bytes (sign and mantissa) and L halfwords
+    uint8_t *l_buf = buf + 16 * h_units;
+#pragma unroll
+    for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) {
+        const uint32_t m = ind[tt];
+        const u32x2 sel = compact[m];
+        uint32_t b[4]; // bytes 0 and 2: sign << 7 | mantissa of the pair
+#pragma unroll
+        for (int c = 0; c < 4; ++c) b[c] = (v[tt][c] & 0x007F007Fu) | ((v[tt][c] >> 8) & 0x00800080u);
+        const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x06040200u), hi = __builtin_amdgcn_perm(b[3], b[2], 0x06040200u);
+        const uint64_t row = __builtin_amdgcn_perm(hi, lo, sel.x) | (uint64_t)__builtin_amdgcn_perm(hi, lo, sel.y) << 32;
+        const uint32_t sh = 8 * (before[tt] & 3u);
+        const uint64_t low = row << sh;
+        const uint32_t top = (uint32_t)(row >> 32 >> 8) >> (24 - sh);
+        uint32_t *at = reinterpret_cast<uint32_t *>(buf + (before[tt] & ~3u));
+        // (a row that ends at an exact dword leaves zeros for the words behind it: not touched, they
+        // may lie in the L segment)
+        if ((uint32_t)low) __hip_atomic_fetch_or(at, (uint32_t)low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if ((uint32_t)(low >> 32)) __hip_atomic_fetch_or(at + 1, (uint32_t)(low >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (top) __hip_atomic_fetch_or(at + 2, top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        uint32_t l_at = 2u * (512u * tt + 8u * lane - before[tt]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (!((m >> e) & 1u)) {
+                *reinterpret_cast<uint16_t *>(l_buf + l_at) = (uint16_t)(v[tt][e >> 1] >> (16 * (e & 1)));
+                l_at += 2;
+            }
+    }
+    lds_done();
+    // the segments as the offsets bound them (the same sizes, unless W changed during the call)
+    const uint32_t h0 = offsets[2 * (size_t)bt], l0 = offsets[2 * (size_t)bt + 1];
+    const uint32_t h_room = offsets[2 * (size_t)bt + 2] - h0, l_room = offsets[2 * (size_t)bt + 3] - l0;
+    send(off_H + (uint64_t)h0 * 16, buf, min(h_units, h_room), ZS_BT_ELEMS / 16);
+    send(off_L + (uint64_t)l0 * 16, l_buf, min(l_units, l_room), ZS_BT_ELEMS / 8);
 }
 
 } // namespace
@@ -215,29 +429,22 @@ extern "C" int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int
     Totals *totals_dev = reinterpret_cast<Totals *>(ws + kTotalsAt);
     auto ok = [](hipError_t e) { return e == hipSuccess; };
 
-    // ---- window (Algorithm 1, phase I)
-    hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(256), 0, s, ws, (uint64_t)ZS_ENCODE_WORKSPACE_BYTES);
-    hipLaunchKernelGGL(hist_kernel, dim3(n_bt), dim3(256), 0, s, W_dev, ldw, k_blocks, hist_dev);
-    uint64_t hist[kHistWords];
-    if (!ok(hipGetLastError()) || !ok(hipMemcpyAsync(hist, hist_dev, sizeof hist, hipMemcpyDeviceToHost, s)) ||
-        !ok(hipStreamSynchronize(s)))
-        return ZS_ERR_HIP;
-    uint64_t window_sum = 0;
-    for (int j = 0; j < ZS_WINDOW; ++j) window_sum += hist[j];
-    uint64_t best_sum = window_sum;
-    int win_lo = 0;
-    for (int st = 1; st + ZS_WINDOW <= 256; ++st) {
-        window_sum += hist[st + ZS_WINDOW - 1] - hist[st - 1];
-        if (window_sum > best_sum) best_sum = window_sum, win_lo = st; // strict: the smallest start wins a tie
-    }
-
-    // ---- segment offsets
     const uint64_t off_bitmaps = 0;
     const uint64_t off_offsets = align_up((uint64_t)n_bt * ZS_BT_BITMAP_BYTES, ZS_SECTION_ALIGN);
     const uint64_t off_H = align_up(off_offsets + ((uint64_t)n_bt + 1) * 8, ZS_SECTION_ALIGN);
     uint32_t *offsets_dev = reinterpret_cast<uint32_t *>(blob + off_offsets);
-    hipLaunchKernelGGL(count_kernel, dim3(n_bt), dim3(256), 0, s, W_dev, ldw, k_blocks, (uint32_t)win_lo, offsets_dev);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, offsets_dev, n_bt, totals_dev);
+
+    // ---- window and counts (Algorithm 1, phase I), segment offsets, then the tiles (phase II)
+    const uint32_t wgs = (uint32_t)(2 * zs_compute_units());
+    auto at_most = [](uint64_t want, uint32_t limit) { return dim3((unsigned)(want < limit ? want : limit)); };
+    hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(1024), 0, s, W_dev, N, K, ldw, hist_dev, totals_dev);
+    hipLaunchKernelGGL(hist_kernel, at_most((n_bt + kHistWaves - 1) / kHistWaves, wgs), dim3(64 * kHistWaves), 0, s, W_dev, ldw, k_blocks,
+                       n_bt, hist_dev, totals_dev, offsets_dev);
+    hipLaunchKernelGGL(recount_kernel, at_most((n_bt + 3) / 4, 4 * wgs), dim3(256), 0, s, W_dev, ldw, k_blocks, n_bt, hist_dev, totals_dev,
+                       offsets_dev);
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, offsets_dev, n_bt, hist_dev, totals_dev);
+    hipLaunchKernelGGL(pack_kernel, dim3((n_bt + 3) / 4 + 1), dim3(256), 0, s, W_dev, ldw, k_blocks, n_bt, totals_dev, blob,
+                       (uint64_t)blob_cap, offsets_dev, off_offsets, off_H);
     Totals tot;
     if (!ok(hipGetLastError()) || !ok(hipMemcpyAsync(&tot, totals_dev, sizeof tot, hipMemcpyDeviceToHost, s)) ||
         !ok(hipStreamSynchronize(s)))
@@ -246,24 +453,12 @@ extern "C" int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int
     const uint64_t total = align_up(off_L + tot.l_units * 16, ZS_SECTION_ALIGN);
     if (total > blob_cap) return ZS_ERR_SIZE;
 
-    // ---- gaps between the sections, then the tiles (Algorithm 1, phase II)
-    auto zero = [&](uint64_t from, uint64_t to) {
-        if (to > from) hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(256), 0, s, blob + from, to - from);
-    };
-    zero((uint64_t)n_bt * ZS_BT_BITMAP_BYTES, off_offsets);
-    zero(off_offsets + ((uint64_t)n_bt + 1) * 8, off_H);
-    zero(off_H + tot.h_units * 16, off_L);
-    zero(off_L + tot.l_units * 16, total);
-    hipLaunchKernelGGL(pack_kernel, dim3((n_bt + 3) / 4), dim3(256), 0, s, W_dev, ldw, k_blocks, n_bt, (uint32_t)win_lo, blob,
-                       (uint64_t)blob_cap, off_bitmaps, offsets_dev, off_H, off_L);
-    if (!ok(hipGetLastError())) return ZS_ERR_HIP;
-
     std::memset(out, 0, sizeof *out);
     out->magic = ZS_MAGIC;
     out->version = ZS_FORMAT_VERSION;
     out->N = N;
     out->K = K;
-    out->base_exp = win_lo - 1;
+    out->base_exp = (int32_t)tot.win_lo - 1;
     out->tile_cfg = ZS_TILE_CFG_FT8_TT16x32_BT64;
     out->n_high = tot.n_high;
     out->n_fallback = (uint64_t)N * (uint64_t)K - tot.n_high;

@@ -343,3 +343,27 @@ def test_error_paths(gu):
         binding.zs_gemm(d, dev, a, c, 4, lda=32, **kw)
     with pytest.raises(binding.ZsError):
         binding.zs_decompress(d, dev, None)
+
+
+def tied_windows(N, K):
+    """Exponents 100..115 in equal shares: every window inside covers the same, the smallest start
+    wins, and a prediction from a part of the weights has no reason to agree."""
+    return (((np.arange(N * K, dtype=np.uint32) % 16 + 100) << 7) | (np.arange(N * K, dtype=np.uint32) // 16 % 128)).astype(np.uint16).reshape(N, K)
+
+
+@pytest.mark.parametrize("kind,N,K", [("tied", 128, 192), ("tied", 1024, 1088), ("gauss", 192, 64 * 2732), ("student_t", 64, 576)])
+def test_encode_device_prediction_and_scan_edges(kind, N, K):
+    """Windows the sample cannot predict (the counts are taken again), and numbers of BlockTiles at the
+    edges of the prefix sum (8196 = one round of 8192 and half a thread more, 9 = one thread and one)."""
+    import torch
+    W = tied_windows(N, K) if kind == "tied" else inputs.make_weights(kind, N, K, seed=91)
+    blob, d = binding.zs_encode(W)
+    assert kind != "tied" or d.base_exp == 99
+    cap = binding.zs_encode_bound(N, K)
+    out = torch.full((cap,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = torch.full((binding.ZS_ENCODE_WORKSPACE_BYTES,), 0xFF, dtype=torch.uint8, device="cuda")
+    d_dev = binding.zs_encode_device(torch.from_numpy(W.view(np.int16)).cuda(), N, K, out, cap, ws)
+    assert desc_fields(d_dev) == desc_fields(d)
+    got = out.cpu().numpy()
+    assert np.array_equal(got[:d.total_bytes], blob)
+    assert (got[d.total_bytes:] == 0xA5).all()
