@@ -283,7 +283,8 @@ struct TileLoads {
 
 // The loads are issued in reverse order of first use: LDS returns data in order, so the wait
 // for the first value used (the H words) also covers all the others and is the only one.
-template <int T, uint32_t LX>
+// MANY leaves out the first two fallbacks and their selectors.
+template <int T, uint32_t LX, bool MANY>
 __device__ __forceinline__ TileLoads load_tt(uint32_t tab, const HalfIndex &hi, uint32_t l_lane)
 {
     constexpr int i = T % 4;
@@ -293,11 +294,13 @@ __device__ __forceinline__ TileLoads load_tt(uint32_t tab, const HalfIndex &hi, 
     q.m = m;
     q.hpos = hi.hpos[i];
     const uint32_t ma = (m << 4) + tab;
-    q.fsel = lds_u32x4<kFselOff>(ma);
+    if constexpr (!MANY) q.fsel = lds_u32x4<kFselOff>(ma);
     // l_lane - 2 hpos in one instruction (LDS addresses are far below 2^23)
     asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(q.lpos) : "v"(q.hpos), "v"(l_lane));
     const uint32_t la = q.lpos & ~3u;
-    if constexpr (kLposStep * T + LX + 4 <= 1020) {
+    if constexpr (MANY) {
+        // load_fallbacks reads them
+    } else if constexpr (kLposStep * T + LX + 4 <= 1020) {
         q.l0 = lds_u32<kLposStep * T + LX>(la);
         q.l1 = lds_u32<kLposStep * T + LX + 4>(la);
     } else {
@@ -316,13 +319,51 @@ __device__ __forceinline__ TileLoads load_tt(uint32_t tab, const HalfIndex &hi, 
     return q;
 }
 
-// Assembles the lane's eight BF16 weights of TensorCoreTile t from its loads.
-// CAREFUL = false handles rows with at most two fallbacks (branch-free); CAREFUL = true adds
-// a per-lane loop for the third and later fallbacks of a row, and reads every fallback from
-// global memory when the L segment did not fit the staged window.
-template <bool BASE_M1, bool CAREFUL, uint32_t LX>
-__device__ __forceinline__ u32x4 finish_tt(int t, const TileLoads &q, const FallbackSource &fs)
+// The fallbacks of a row that has more than two: for each output register k the two halfwords that
+// start at its first fallback, and the v_perm selector that drops them into it.  The selector
+// depends on the register's two indicator bits alone: word 0 of FSEL entry (m >> 2 k) & 3.
+struct RowFallbacks {
+    uint32_t a0[4], a1[4]; // 8 bytes around the pair
+    uint32_t lpos[4];      // the pair's LDS address (minus kLposStep * t + LX)
+    uint32_t sel[4];
+};
+template <int T, uint32_t LX>
+__device__ __forceinline__ RowFallbacks load_fallbacks(uint32_t tab, const TileLoads &q)
 {
+    RowFallbacks f;
+    const uint32_t fb = q.m ^ 0xFFu;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        f.lpos[k] = k ? q.lpos + 2 * __builtin_popcount(fb & ((1u << (2 * k)) - 1u)) : q.lpos;
+        const uint32_t la = f.lpos[k] & ~3u;
+        if constexpr (kLposStep * T + LX + 4 <= 1020) {
+            f.a0[k] = lds_u32<kLposStep * T + LX>(la);
+            f.a1[k] = lds_u32<kLposStep * T + LX + 4>(la);
+        } else {
+            f.a0[k] = lds_u32_single<kLposStep * T + LX>(la);
+            f.a1[k] = lds_u32_single<kLposStep * T + LX + 4>(la);
+        }
+        f.sel[k] = lds_u32<kFselOff>(((k < 2 ? q.m << (4 - 2 * k) : q.m >> (2 * k - 4)) & 0x30u) + tab);
+    }
+    return f;
+}
+
+// Assembles the lane's eight BF16 weights of TensorCoreTile t from its loads.
+// kFew handles rows with at most two fallbacks, the others any number, and read every fallback
+// from global memory, one at a time in a per-lane loop, when the L segment did not fit the staged
+// window.  kLoop takes the third and later fallbacks of a row one at a time as well, kMany takes
+// them register by register without a branch (load_fallbacks).  Which of the two a matrix gets is
+// its fallback density (decode_block_tile): a loop costs little where a wave finds one such row now and
+// then, and up to six rounds of an LDS read and an insertion where it finds many.  Measured at 16
+// tokens, kLoop / kMany: 4096 x 14336, a third of the weights outside the window, 74.7 / 32.8 us;
+// 28672 x 4096 N(0, 0.02), 2 % of them, 40.0 / 40.6 us.
+enum Fallbacks { kFew, kLoop, kMany };
+template <bool BASE_M1, Fallbacks FB, int T, uint32_t LX>
+__device__ __forceinline__ u32x4 finish_tt(uint32_t tab, const TileLoads &q, const FallbackSource &fs)
+{
+    RowFallbacks f;
+    if constexpr (FB == kMany) f = load_fallbacks<T, LX>(tab, q);
+
     // -- funnel shift (v_alignbyte_b32 uses only the two low bits of its shift operand)
     const uint32_t hpos = q.hpos;
     const uint32_t h0 = __builtin_amdgcn_alignbyte(q.d1, q.d0, hpos);
@@ -353,19 +394,23 @@ __device__ __forceinline__ u32x4 finish_tt(int t, const TileLoads &q, const Fall
     r.z = ((e_hi << 7) & kExpMask) | (r.z & ~kExpMask);
     r.w = ((e_hi >> 1) & kExpMask) | (r.w & ~kExpMask);
 
-    // -- fallback path, common case: the first two raw BF16 of the row, placed with v_perm
-    //    (done for every lane: rows without fallbacks have identity selectors)
-    const uint32_t lpos = q.lpos;
-    const uint32_t lv = __builtin_amdgcn_alignbyte(q.l1, q.l0, lpos);
-    r.x = __builtin_amdgcn_perm(lv, r.x, q.fsel.x);
-    r.y = __builtin_amdgcn_perm(lv, r.y, q.fsel.y);
-    r.z = __builtin_amdgcn_perm(lv, r.z, q.fsel.z);
-    r.w = __builtin_amdgcn_perm(lv, r.w, q.fsel.w);
-
-    if (CAREFUL) {
+    if constexpr (FB != kMany) {
+        // -- fallback path, common case: the first two raw BF16 of the row, placed with v_perm
+        //    (done for every lane: rows without fallbacks have identity selectors)
+        const uint32_t lv = __builtin_amdgcn_alignbyte(q.l1, q.l0, q.lpos);
+        r.x = __builtin_amdgcn_perm(lv, r.x, q.fsel.x);
+        r.y = __builtin_amdgcn_perm(lv, r.y, q.fsel.y);
+        r.z = __builtin_amdgcn_perm(lv, r.z, q.fsel.z);
+        r.w = __builtin_amdgcn_perm(lv, r.w, q.fsel.w);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            r[k] = __builtin_amdgcn_perm(__builtin_amdgcn_alignbyte(f.a1[k], f.a0[k], f.lpos[k]), r[k], f.sel[k]);
+    }
+    if (FB == kLoop || (FB == kMany && fs.from_global)) {
         uint32_t fb = q.m ^ 0xFFu;
-        uint32_t pos = lpos + kLposStep * (uint32_t)t + LX;
-        if (!fs.from_global) { // the first two are in place already
+        uint32_t pos = q.lpos + kLposStep * (uint32_t)T + LX;
+        if (FB == kLoop && !fs.from_global) { // the first two are in place already
             fb &= fb - 1;
             fb &= fb - 1;
             pos += 4;
@@ -377,7 +422,7 @@ __device__ __forceinline__ u32x4 finish_tt(int t, const TileLoads &q, const Fall
             // in the branch.  A wait placed after the join would cover both sources, and the
             // one for global memory also waits for the LDS-direct loads of the next tile.
             uint32_t v;
-            if (fs.from_global) {
+            if (FB == kMany || fs.from_global) {
                 v = fs.l_glob[(pos - fs.l_at) >> 1];
                 asm volatile("" : "+v"(v));
             } else {
@@ -396,67 +441,70 @@ __device__ __forceinline__ u32x4 finish_tt(int t, const TileLoads &q, const Fall
 // before tile t is assembled.  The second half's plane bytes (at pa + EXTRA, see read_planes)
 // are read while tile 1 is assembled and indexed before tile 3 is.  sink(t, weights) receives
 // each tile's registers.  Each half runs branch-free when none of its rows has more than two
-// fallbacks, else in its "careful" variant (also when the L segment did not fit the staged
+// fallbacks, else in its "careful" variant CAREFUL (also when the L segment did not fit the staged
 // window).
-template <bool BASE_M1, uint32_t EXTRA, uint32_t LX, class Sink>
+template <bool BASE_M1, uint32_t EXTRA, uint32_t LX, Fallbacks CAREFUL, class Sink>
 __device__ __forceinline__ void decode_block_tile(uint32_t tab, uint32_t pa, const HalfIndex &h0, uint32_t h_base,
                                                   uint32_t l_lane, const FallbackSource &fs, Sink sink)
 {
 #define ZS_STAGE_BARRIER __builtin_amdgcn_sched_barrier(0)
+    using Careful = std::integral_constant<Fallbacks, CAREFUL>;
     HalfIndex h1;
     TileLoads q4;
-    auto first = [&](auto careful) {
-        constexpr bool C = decltype(careful)::value;
-        TileLoads q = load_tt<0, LX>(tab, h0, l_lane);
-        TileLoads nq = load_tt<1, LX>(tab, h0, l_lane);
+    auto first = [&](auto variant) {
+        constexpr Fallbacks F = decltype(variant)::value;
+        constexpr bool C = F == kMany;
+        TileLoads q = load_tt<0, LX, C>(tab, h0, l_lane);
+        TileLoads nq = load_tt<1, LX, C>(tab, h0, l_lane);
         ZS_STAGE_BARRIER;
-        sink(0, finish_tt<BASE_M1, C, LX>(0, q, fs));
+        sink(0, finish_tt<BASE_M1, F, 0, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
         q = nq;
-        nq = load_tt<2, LX>(tab, h0, l_lane);
+        nq = load_tt<2, LX, C>(tab, h0, l_lane);
         read_planes<EXTRA, 1, true>(pa, h1);
         ZS_STAGE_BARRIER;
-        sink(1, finish_tt<BASE_M1, C, LX>(1, q, fs));
+        sink(1, finish_tt<BASE_M1, F, 1, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
         q = nq;
-        nq = load_tt<3, LX>(tab, h0, l_lane);
+        nq = load_tt<3, LX, C>(tab, h0, l_lane);
         ZS_STAGE_BARRIER;
-        sink(2, finish_tt<BASE_M1, C, LX>(2, q, fs));
+        sink(2, finish_tt<BASE_M1, F, 2, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
         q = nq;
         index_half<false>(h_base, h1);
-        q4 = load_tt<4, LX>(tab, h1, l_lane);
+        q4 = load_tt<4, LX, false>(tab, h1, l_lane);
         ZS_STAGE_BARRIER;
-        sink(3, finish_tt<BASE_M1, C, LX>(3, q, fs));
+        sink(3, finish_tt<BASE_M1, F, 3, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
     };
     if (fs.from_global || __builtin_amdgcn_ballot_w64(h0.min_cnt < 6) != 0)
-        first(std::true_type{});
+        first(Careful{});
     else
-        first(std::false_type{});
-    auto second = [&](auto careful) {
-        constexpr bool C = decltype(careful)::value;
+        first(std::integral_constant<Fallbacks, kFew>{});
+    auto second = [&](auto variant) {
+        constexpr Fallbacks F = decltype(variant)::value;
+        constexpr bool C = F == kMany;
         TileLoads q = q4;
-        TileLoads nq = load_tt<5, LX>(tab, h1, l_lane);
+        TileLoads nq = load_tt<5, LX, C>(tab, h1, l_lane);
         ZS_STAGE_BARRIER;
-        sink(4, finish_tt<BASE_M1, C, LX>(4, q, fs));
-        ZS_STAGE_BARRIER;
-        q = nq;
-        nq = load_tt<6, LX>(tab, h1, l_lane);
-        ZS_STAGE_BARRIER;
-        sink(5, finish_tt<BASE_M1, C, LX>(5, q, fs));
+        sink(4, finish_tt<BASE_M1, F, 4, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
         q = nq;
-        nq = load_tt<7, LX>(tab, h1, l_lane);
+        nq = load_tt<6, LX, C>(tab, h1, l_lane);
         ZS_STAGE_BARRIER;
-        sink(6, finish_tt<BASE_M1, C, LX>(6, q, fs));
+        sink(5, finish_tt<BASE_M1, F, 5, LX>(tab, q, fs));
         ZS_STAGE_BARRIER;
-        sink(7, finish_tt<BASE_M1, C, LX>(7, nq, fs));
+        q = nq;
+        nq = load_tt<7, LX, C>(tab, h1, l_lane);
+        ZS_STAGE_BARRIER;
+        sink(6, finish_tt<BASE_M1, F, 6, LX>(tab, q, fs));
+        ZS_STAGE_BARRIER;
+        sink(7, finish_tt<BASE_M1, F, 7, LX>(tab, nq, fs));
     };
     if (fs.from_global || __builtin_amdgcn_ballot_w64(h1.min_cnt < 6) != 0)
-        second(std::true_type{});
+        second(Careful{});
     else
-        second(std::false_type{});
+        second(std::integral_constant<Fallbacks, kFew>{});
 #undef ZS_STAGE_BARRIER
 }
 

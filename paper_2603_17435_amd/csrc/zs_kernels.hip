@@ -35,6 +35,9 @@ struct Slot {
     static constexpr uint32_t kBytes = kL + LW + 64;
     static constexpr int kLChunks = (LW + 1023) / 1024;
     static constexpr int kLoads = 2 + 4 + kLChunks; // LDS-direct instructions per BlockTile
+    // A matrix with few fallbacks gets the short window (pick_l_window): then rows with more than two
+    // of them are rare and the loop is the better one, else they are the rule.
+    static constexpr Fallbacks kCareful = LW == 512 ? kLoop : kMany;
     // what the LDS-direct loads of a tile can write: 1536 bytes of bit-planes, four 1 KB pieces of
     // H, kLChunks pieces of L (one 512-byte piece for LW = 512); all of it lies inside the slot
     static_assert(kPlanes + ZS_BT_BITMAP_BYTES <= kH && kH + 4 * 1024 <= kL, "sections of a slot overlap");
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
         const FallbackSource fs = {slot + S::kL, reinterpret_cast<const uint16_t *>(sg.l), sg.l_bytes > (uint32_t)LW};
         const uint32_t strip = bt / (uint32_t)bv.k_blocks, kb = bt % (uint32_t)bv.k_blocks;
         uint16_t *dst = out + ((int64_t)strip * 64 + row_in_tt) * ldw + (int64_t)kb * 64 + col_in_tt;
-        decode_block_tile<BASE_M1, 0, 0>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
+        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
                                          [&](int tt, const u32x4 &w) {
                                              __builtin_nontemporal_store(
                                                  w, reinterpret_cast<u32x4 *>(dst + (int64_t)((tt & 3) * 16) * ldw + (tt >> 2) * 32));
@@ -737,7 +740,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
             for (int j = 0; j < MT; ++j) {
                 bop[kh][j] = __builtin_bit_cast(bf16x8, bfrag[kh][j]);
             }
-        decode_block_tile<BASE_M1, CUR * S::kBytes, kLX>(tab, pa0, h0, h_base, l_lane0, fs, [&](int tt, const u32x4 &w) {
+        decode_block_tile<BASE_M1, CUR * S::kBytes, kLX, S::kCareful>(tab, pa0, h0, h_base, l_lane0, fs, [&](int tt, const u32x4 &w) {
             const bf16x8 wop = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
             for (int j = 0; j < MT; ++j)
@@ -1002,7 +1005,7 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         const uint32_t i = s_i[CUR], dslot = i % (uint32_t)R, need = (uint32_t)q_active * (i / (uint32_t)R);
         while ((int32_t)(uniform(lds_poll(ctl + kPcConsumed + 4 * dslot)) - need) < 0) __builtin_amdgcn_s_sleep(1);
         const uint32_t out = dense0 + dslot * kDenseBytes + lane * 16;
-        decode_block_tile<BASE_M1, 0, 0>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
+        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
                                          [&](int tt, const u32x4 &w) {
                                              *((__attribute__((address_space(3))) u32x4 *)(out + tt * 1024)) = w;
                                          });

@@ -71,6 +71,25 @@ def test_gemm_adversarial_small(gu, kind, M):
     gu.check_gemm(W, A)
 
 
+@pytest.mark.parametrize("per_row", [2, 3, 5, 7, 8, None])
+def test_rows_with_many_fallbacks(gu, per_row):
+    """FragTile rows with a given number of out-of-window elements at random places (None: any number
+    from 0 to 8 by turns), in a matrix that has enough of them for the long L window."""
+    rng = np.random.default_rng(50 + (per_row or 0))
+    W = inputs.gaussian_weights(192, 448, 51)
+    rows = W.reshape(-1, 8)                     # eight consecutive k = one FragTile row
+    hit = rng.random(len(rows)) < 0.4
+    count = rng.integers(0, 9, len(rows)) if per_row is None else np.full(len(rows), per_row)
+    place = rng.random(rows.shape).argsort(1) < np.where(hit, count, 0)[:, None]
+    far = (rng.integers(0, 1 << 16, rows.shape) & 0x80FF) | (rng.integers(1, 60, rows.shape) << 8)
+    W = np.where(place, far.astype(np.uint16), rows).reshape(W.shape).astype(np.uint16)
+    _, d = binding.zs_encode(W)
+    assert 2 * d.n_fallback / (3 * 7) > 256     # bytes per BlockTile: beyond the short window
+    assert np.array_equal(gu.gpu_decompress(W), W)
+    for M in (5, 31, 40, 77):                   # every kernel that decodes
+        gu.check_gemm(W, inputs.activations(M, 448, 52 + M))
+
+
 def test_gemm_specials(gu):
     """Finite specials: numeric check.  Inf/NaN: class check (NaN <-> NaN, Inf same sign)."""
     A = inputs.activations(16, 256, 9)
