@@ -759,12 +759,12 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
 }
 
 // --------------------------------------------------------------------------------------
-// ZipGEMM, wider M (up to 64 MT tokens per launch): producer and consumer waves.
+// ZipGEMM, wider M (up to 16 MT Q tokens per launch): producer and consumer waves.
 //
 // The decode cost of a BlockTile does not depend on M, so for more than a few tokens it is
 // paid once per workgroup and shared: P producer waves stream and decode BlockTiles exactly
-// as above but write the decoded weights, already in MFMA A-operand lane order, to a ring of
-// R dense tiles in LDS (8 KB each); up to Q consumer waves, each owning 16 MT tokens,
+// as above but hand the decoded weights on, already in MFMA operand lane order, through a ring
+// of R dense tiles in LDS (8 KB each); up to Q consumer waves, each owning 16 MT tokens,
 // read every dense tile and run the MFMAs against their own activation fragments.  A token
 // belongs to one consumer, so nothing is reduced across waves: a consumer stores (whole
 // strip) or atomically adds (strip shared between workgroups) its registers when the strip
@@ -775,17 +775,48 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
 // range lives in dense slot i % R.  ready[slot] = i + 1 once tile i is complete in LDS;
 // consumed[slot] counts consumer passes over the slot.  A producer may write tile i when
 // consumed[slot] has reached q_active * (i / R); a consumer reads tile i when ready[slot] is
-// i + 1.  Every wait points to a strictly smaller tile index and tiles are handed out in
-// order, so the smallest unfinished tile can always complete.
+// i + 1, and still holds slot (i - 1) % R while it waits for that, so R is at least 2.  Tiles
+// are handed out in order and a producer waits for the consumption of an earlier tile than its
+// own, so the smallest unfinished tile can always complete.
+//
+// A producer decodes into registers and claims its dense slot only to write the finished tile:
+// were the slot held for the whole decode, R slots would allow R tiles in all the stages from
+// decode to consumption, fewer than there are producers plus consumers' backlog.
 // --------------------------------------------------------------------------------------
+
+// acc[j] += frag[j] * w for the MT token blocks of a consumer, in place.  Written out because the
+// compiler's own MFMAs write to other registers than they add to: 153 registers with 32 tokens to a
+// consumer where sixteen waves have 128 each.  The leading s_nop covers an operand that a vector
+// instruction has just written (two wait states); an accumulator is next touched by the MFMAs of the
+// next half tile, or after accumulators_done().
+template <int MT>
+__device__ __forceinline__ void mfma_rows(f32x4 (&acc)[MT], const u32x4 (&frag)[MT], const u32x4 &w)
+{
+    static_assert(MT == 1 || MT == 2, "operands below");
+#define ZS_MFMA(I, A, W) "v_mfma_f32_16x16x32_bf16 %" #I ", %" #A ", %" #W ", %" #I "\n\t"
+    if constexpr (MT == 1)
+        asm volatile("s_nop 1\n\t" ZS_MFMA(0, 1, 2) : "+v"(acc[0]) : "v"(frag[0]), "v"(w));
+    else
+        asm volatile("s_nop 1\n\t" ZS_MFMA(0, 2, 4) ZS_MFMA(1, 3, 4) : "+v"(acc[0]), "+v"(acc[1]) : "v"(frag[0]), "v"(frag[1]), "v"(w));
+#undef ZS_MFMA
+}
+// Before anything but an MFMA reads or writes accumulators: the last MFMA's four passes plus the write
+// are over (sixteen wait states, seven are needed).
+template <int MT>
+__device__ __forceinline__ void accumulators_done(f32x4 (&acc)[4][MT])
+{
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+        asm volatile("s_nop 15" : "+v"(acc[0][j]), "+v"(acc[1][j]), "+v"(acc[2][j]), "+v"(acc[3][j]));
+}
 enum : uint32_t { kPcNext = 0, kPcReady = 64, kPcConsumed = 128, kPcCtlBytes = 192, kDenseBytes = 8192 };
 
-template <int MT, int LW, int P, int R, int Q, bool BASE_M1>
+template <int MT, int LW, int P, int R, int Q, int F, bool BASE_M1>
 __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, const uint16_t *A, int64_t lda,
                                                                           float *C, int64_t ldc, int M, int q_active,
                                                                           RangeSplit rs)
 {
-    static_assert(R >= P && R <= 16, "ready / consumed words are laid out for at most 16 dense slots");
+    static_assert(R >= 2 && R <= 16, "two slots at least (above); ready / consumed words are laid out for at most 16");
     using S = Slot<LW>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     build_tables(smem, bv.base_exp);
@@ -793,10 +824,11 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
     const uint32_t lane = threadIdx.x & 63u, wave = uniform(threadIdx.x >> 6);
     const uint32_t tab = dynamic_lds_base();
     const uint32_t ctl = tab + kTableBytes, dense0 = ctl + kPcCtlBytes;
-    const uint32_t m_lane = lane & 15u, kgrp = lane >> 4;
 
     const uint32_t k_blocks = (uint32_t)bv.k_blocks;
-    const uint32_t g0 = rs.begin(blockIdx.x), g1 = rs.begin(blockIdx.x + 1);
+    // neighbouring ranges (which share strips, and slabs of A) on one die, as in gemm_stream_kernel
+    const uint32_t range_id = (gridDim.x & 7u) == 0 ? (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const uint32_t g0 = rs.begin(range_id), g1 = rs.begin(range_id + 1);
 
     for (uint32_t i = threadIdx.x; i < kPcCtlBytes / 4; i += blockDim.x) *((LdsU32)(ctl + 4 * i)) = i == kPcNext / 4 ? g0 : 0u;
     __syncthreads();
@@ -805,123 +837,121 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
 
     if (wave >= (uint32_t)P) {
         // ------------------------------------------------------------------ consumer
+        // What bounds it: the L2 -> CU transfer of the activations (128 M bytes per BlockTile) from about
+        // 200 tokens on, the decode below.  Nothing of a tile may be waited for when it is used, since a
+        // chain of four LDS round trips per tile (poll, operands, fence, hand back) is longer than the
+        // decode: operands are read a tile ahead, "ready" is polled a tile before it is looked at, a
+        // slot is handed back without a fence, and the consumers' waves go first on their SIMD.
+        // 4096 x 14336, 128 / 200 tokens: 61.5 / 88.1 -> 43 / 61 us; 28672 x 4096, 128 / 256: 93.7 / 161 -> 75 / 127 us.
+        __builtin_amdgcn_s_setprio(2);
         const uint32_t c = wave - P;
         if ((int)c >= q_active) return;
+        const uint32_t m_lane = lane & 15u, kgrp = lane >> 4;
         const uint32_t tok0 = c * 16u * MT;
-        // B operand of the 16x16x32 MFMA: lane l holds token l % 16 and the 8 consecutive k that
-        // start at 8 * (l / 16).  Tokens >= M read token 0 instead (their columns are never stored).
+        // A operand of the 16x16x32 MFMA: lane l holds token l % 16 and the 8 consecutive k that
+        // start at 8 * (l / 16).  Tokens >= M read token 0 instead (their rows are never stored).
         uint32_t rowoff[MT];
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
             const uint32_t m = tok0 + j * 16 + m_lane;
             rowoff[j] = ((int)m < M ? m : 0u) * (uint32_t)lda * 2u + kgrp * 16u;
         }
-        const uint8_t *a_bytes = reinterpret_cast<const uint8_t *>(A);
-        // The activation fragments are requested D tiles ahead: an L2 hit costs about as much
-        // time as several tiles' worth of MFMAs.  (With eight consumers a wave has 128 registers,
-        // which hold two tiles' fragments of 32 tokens, not four.)
-        constexpr int D = MT == 1 ? 4 : MT == 2 ? (Q <= 4 ? 4 : 2) : 1;
-        u32x4 frag[D][2][MT];
-        auto load_frags = [&](int d, uint32_t kb) {
+        // Through a buffer descriptor: per-lane row offset + uniform position in k, no address
+        // arithmetic, and nothing is read beyond the last token's row.
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t *>(A), 0, (int)(((uint32_t)M - 1u) * (uint32_t)lda * 2u + k_blocks * 128u), 0x00020000);
+        // F = fragment buffers, one half tile (32 of the 64 k) each, requested F / 2 tiles before they are
+        // used; both halves of a tile together, since they share the cache lines.  (Q = 8: 128 registers
+        // per wave, room for two tiles' worth.)
+        static_assert(F % 2 == 0 && F <= 6, "the loop below");
+        u32x4 frag[F][MT];
+        const uint32_t strip0 = g0 / k_blocks;
+        uint32_t strip = strip0, kb = g0 - strip0 * k_blocks; // of the tile being consumed
+        // k block of the half whose fragments are requested next.  (It wraps around with the strips, so
+        // the F halves asked for beyond the range's end are valid addresses too.)
+        uint32_t req_kb = kb;
+        auto request = [&](int f, int kh) {
 #pragma unroll
-            for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    frag[d][kh][j] = *reinterpret_cast<const u32x4 *>(a_bytes + (size_t)kb * 128 + kh * 64 + rowoff[j]);
+            for (int j = 0; j < MT; ++j) frag[f][j] = __builtin_amdgcn_raw_buffer_load_b128(rows, rowoff[j], req_kb * 128 + 64 * kh, 0);
+            if (kh == 1) req_kb = req_kb + 1 == k_blocks ? 0u : req_kb + 1;
         };
         f32x4 acc[4][MT];
         auto clear_acc = [&]() {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int j = 0; j < MT; ++j)
 #pragma unroll
-                for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < 4; ++i) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         };
         clear_acc();
-        const uint32_t strip0 = g0 / k_blocks;
-        uint32_t strip = strip0, kb = g0 - strip0 * k_blocks; // of the tile being consumed
-        uint32_t kb_ahead = kb;                               // of the tile whose fragments are requested next
-        uint32_t in_strip = 0;                                // tiles of the current strip consumed so far
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if ((uint32_t)d < n_tiles) load_frags(d, kb_ahead);
-            kb_ahead = kb_ahead + 1 == k_blocks ? 0u : kb_ahead + 1;
-        }
-        uint32_t slot = 0, i = 0;
-        // MT = 1: the decoded weights of tile i + 1 are read into a second register set while tile
-        // i is multiplied.  Wider consumers need those registers for accumulators and fragments
-        // and read each operand right before its MFMAs.
-        constexpr bool kPipe = MT == 1;
-        u32x4 wreg[kPipe ? 2 : 1][8];
-        auto wait_ready = [&](uint32_t tile, uint32_t sl) {
-            while (uniform(lds_poll(ctl + kPcReady + 4 * sl)) != tile + 1) __builtin_amdgcn_s_sleep(1);
-            lds_fence();
+        for (int f = 0; f < F; ++f) request(f, f & 1);
+
+        uint32_t slot = 0, i = 0, in_strip = 0; // tile being consumed, tiles of its strip consumed so far
+        // Decoded weights: each operand of the next tile is read as soon as the MFMAs of this tile's are issued.
+        u32x4 w[8];
+        auto poll_ready = [&](uint32_t sl) { return lds_poll(ctl + kPcReady + 4 * sl); };
+        auto wait_ready = [&](uint32_t seen, uint32_t tile, uint32_t sl) {
+            while (uniform(seen) != tile + 1) {
+                __builtin_amdgcn_s_sleep(1);
+                seen = poll_ready(sl);
+            }
+            asm volatile("" ::: "memory");
         };
-        auto read_weights = [&](int p, uint32_t sl) {
-            const uint32_t at = dense0 + sl * kDenseBytes + lane * 16;
+        auto read_weight = [&](int t, uint32_t at) { w[t % 8] = *((const __attribute__((address_space(3))) u32x4 *)(at + t * 1024)); };
+        auto address = [&](uint32_t sl) { return dense0 + sl * kDenseBytes + lane * 16; };
+        wait_ready(poll_ready(0), 0, 0);
 #pragma unroll
-            for (int tt = 0; tt < 8; ++tt) wreg[p][tt] = *((const __attribute__((address_space(3))) u32x4 *)(at + tt * 1024));
-        };
-        auto hand_back = [&](uint32_t sl) {
-            lds_fence(); // the slot's data is in registers
-            if (lane == 0)
-                __hip_atomic_fetch_add((LdsU32)(ctl + kPcConsumed + 4 * sl), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        };
-        if constexpr (kPipe) {
-            wait_ready(0, 0);
-            read_weights(0, 0);
-        }
-        auto consume = [&](auto d_c, auto p_c) {
-            constexpr int d = decltype(d_c)::value, p = kPipe ? decltype(p_c)::value : 0;
-            bf16x8 bop[2][MT];
-#pragma unroll
-            for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                for (int j = 0; j < MT; ++j) {
-                    bop[kh][j] = __builtin_bit_cast(bf16x8, frag[d][kh][j]);
-                }
-            if (i + D < n_tiles) load_frags(d, kb_ahead);
-            kb_ahead = kb_ahead + 1 == k_blocks ? 0u : kb_ahead + 1;
+        for (int t = 0; t < 8; ++t) read_weight(t, address(0));
+        uint32_t seen = poll_ready(1 % R);
+        auto consume = [&](auto f_c) { // buffer of the tile's first half
+            constexpr int f0 = decltype(f_c)::value, f1 = f0 + 1;
             const uint32_t slot_next = slot + 1 == (uint32_t)R ? 0u : slot + 1;
-            if constexpr (kPipe) {
-                hand_back(slot); // tile i was read during the previous step
-                if (i + 1 < n_tiles) {
-                    wait_ready(i + 1, slot_next);
-                    read_weights(p ^ 1, slot_next);
-                }
-            } else {
-                wait_ready(i, slot);
-            }
-            const uint32_t at = dense0 + slot * kDenseBytes + lane * 16;
+            const uint32_t at_next = address(slot_next);
+            if (i + 1 < n_tiles) wait_ready(seen, i + 1, slot_next);
 #pragma unroll
-            for (int tt = 0; tt < 8; ++tt) {
-                const u32x4 w = kPipe ? wreg[p][tt] : *((const __attribute__((address_space(3))) u32x4 *)(at + tt * 1024));
-                const bf16x8 wop = __builtin_bit_cast(bf16x8, w);
-#pragma unroll
-                for (int j = 0; j < MT; ++j)
-                    acc[tt & 3][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wop, bop[tt >> 2][j], acc[tt & 3][j], 0, 0, 0);
+            for (int t = 0; t < 8; ++t) {
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_rows<MT>(acc[t & 3], frag[t < 4 ? f0 : f1], w[t]);
+                __builtin_amdgcn_sched_barrier(0);
+                read_weight(t, at_next); // (after the last tile: bytes that nobody uses)
             }
-            if constexpr (!kPipe) hand_back(slot);
+            // every operand of the tile has been in an MFMA, so the slot has been read: hand it back, and ask
+            // for the state of the tile after the next one (looked at a tile later)
+            asm volatile("" ::: "memory");
+            if (lane == 0)
+                __hip_atomic_fetch_add((LdsU32)(ctl + kPcConsumed + 4 * slot), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            seen = poll_ready(slot_next + 1 == (uint32_t)R ? 0u : slot_next + 1);
+            request(f0, 0); // the halves F further on; both at once: they share the cache lines
+            request(f1, 1);
             ++in_strip;
             const bool last_of_strip = kb + 1 == k_blocks;
             if (last_of_strip || i + 1 == n_tiles) {
-                // D layout of the 16x16 MFMA: a lane holds token lane % 16 and rows 4 * (lane / 16) .. + 3
+                // D layout of the 16x16 MFMA with the activations as A operand: a lane holds feature
+                // lane % 16 and tokens 4 * (lane / 16) .. + 3, so that the 64 lanes of a store or an
+                // atomic cover four runs of 64 bytes (with the operands the other way round an
+                // atomic touches 16 rows, four words each)
+                // (one per-lane offset, formed here from a copy of the lane number the compiler cannot
+                // see through, and uniform rows: as per-lane row addresses they do not fit the registers)
                 const bool whole = in_strip == k_blocks;
+                accumulators_done<MT>(acc);
+                uint32_t l = lane;
+                asm volatile("" : "+v"(l));
+                const int64_t lane_at = (int64_t)(4 * (l >> 4)) * ldc + (l & 15u);
+                float *row0 = C + (int64_t)tok0 * ldc + (int64_t)strip * 64;
 #pragma unroll
-                for (int j = 0; j < MT; ++j) {
-                    const uint32_t m = tok0 + j * 16 + m_lane;
-                    if ((int)m < M) {
+                for (int j = 0; j < MT; ++j)
 #pragma unroll
-                        for (int rb = 0; rb < 4; ++rb) {
-                            float *dst = C + (int64_t)m * ldc + (int64_t)strip * 64 + rb * 16 + 4 * kgrp;
-                            if (whole) {
-                                *reinterpret_cast<f32x4 *>(dst) = acc[rb][j];
-                            } else {
+                    for (int e = 0; e < 4; ++e) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        float *dst = row0 + (int64_t)(j * 16 + e) * ldc + lane_at;
+                        if ((int)(tok0 + j * 16 + e + 4 * (l >> 4)) < M) {
 #pragma unroll
-                                for (int e = 0; e < 4; ++e) unsafeAtomicAdd(dst + e, acc[rb][j][e]);
+                            for (int rb = 0; rb < 4; ++rb) {
+                                if (whole) dst[16 * rb] = acc[rb][j][e];
+                                else unsafeAtomicAdd(dst + 16 * rb, acc[rb][j][e]);
                             }
                         }
                     }
-                }
                 clear_acc();
                 in_strip = 0;
                 ++strip;
@@ -930,22 +960,16 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
             slot = slot_next;
             ++i;
         };
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        using I3 = std::integral_constant<int, 3>;
-        for (;;) {
+        for (;;) { // F is even: the buffers' roles repeat every F / 2 tiles
             if (i >= n_tiles) break;
-            consume(I0{}, I0{});
-            if constexpr (D > 1) {
+            consume(std::integral_constant<int, 0>{});
+            if constexpr (F > 2) {
                 if (i >= n_tiles) break;
-                consume(I1{}, I1{});
+                consume(std::integral_constant<int, 2>{});
             }
-            if constexpr (D > 2) {
+            if constexpr (F > 4) {
                 if (i >= n_tiles) break;
-                consume(I2{}, I0{});
-                if (i >= n_tiles) break;
-                consume(I3{}, I1{});
+                consume(std::integral_constant<int, 4>{});
             }
         }
         return;
@@ -1000,15 +1024,17 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         uint32_t h_base = slot + S::kH;
         index_half<true>(h_base, h0);
         const FallbackSource fs = {slot + S::kL, reinterpret_cast<const uint16_t *>(s_l[CUR].l), s_l[CUR].big != 0};
+        u32x4 dec[8];
+        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
+                                         [&](int tt, const u32x4 &w) { dec[tt] = w; });
 
         // the dense slot must have been read by every consumer before it is overwritten
         const uint32_t i = s_i[CUR], dslot = i % (uint32_t)R, need = (uint32_t)q_active * (i / (uint32_t)R);
         while ((int32_t)(uniform(lds_poll(ctl + kPcConsumed + 4 * dslot)) - need) < 0) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory"); // no write of the tile moves above the poll
         const uint32_t out = dense0 + dslot * kDenseBytes + lane * 16;
-        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
-                                         [&](int tt, const u32x4 &w) {
-                                             *((__attribute__((address_space(3))) u32x4 *)(out + tt * 1024)) = w;
-                                         });
+#pragma unroll
+        for (int tt = 0; tt < 8; ++tt) *((__attribute__((address_space(3))) u32x4 *)(out + tt * 1024)) = dec[tt];
         lds_fence(); // the tile is complete in LDS before it is announced
         if (lane == 0)
             __hip_atomic_store((LdsU32)(ctl + kPcReady + 4 * dslot), i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1134,7 +1160,7 @@ struct GemmVariant {
 const GemmVariant kVariants[] = {
     {"m16_l0_w11", 1, 512, 11, 0}, {"m16_l0_w8", 1, 512, 8, 0},   {"m32_l0_w10", 2, 512, 10, 0},
     {"m32_l0_w7", 2, 512, 7, 0},   {"m16_l4_w7", 1, 4096, 7, 0},  {"m32_l4_w6", 2, 4096, 6, 0},
-    {"p64_l0_w7", 1, 512, 7, 4},   {"p128_l0_w7", 2, 512, 7, 4},  {"p256_l0_w7", 2, 512, 7, 8},
+    {"p64_l0_w7", 1, 512, 7, 4},   {"p128_l0_w8", 2, 512, 8, 4},  {"p256_l0_w8", 2, 512, 8, 8},
     {"p64_l4_w5", 1, 4096, 5, 4},  {"p128_l4_w5", 2, 4096, 5, 4}, {"p256_l4_w5", 2, 4096, 5, 8},
     {"m64_l0_w7", 4, 512, 7, 0},   {"m64_l4_w5", 4, 4096, 5, 0},
 };
@@ -1199,7 +1225,7 @@ int launch_gemm(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, in
     return hipGetLastError() == hipSuccess ? ZS_OK : ZS_ERR_HIP;
 }
 
-template <int MT, int LW, int P, int R, int Q>
+template <int MT, int LW, int P, int R, int Q, int F>
 int launch_pc(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int64_t ldc, int M, uint32_t wgs,
               int device, hipStream_t s)
 {
@@ -1209,7 +1235,7 @@ int launch_pc(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int6
     static_assert(S::kLoads < 64, "vmcnt cannot count that many loads");
     static std::atomic<uint64_t> lds_allowed[2];
     const bool m1 = bv.base_exp < 0;
-    auto kern = m1 ? gemm_pc_kernel<MT, LW, P, R, Q, true> : gemm_pc_kernel<MT, LW, P, R, Q, false>;
+    auto kern = m1 ? gemm_pc_kernel<MT, LW, P, R, Q, F, true> : gemm_pc_kernel<MT, LW, P, R, Q, F, false>;
     int rc = allow_big_lds(kern, lds, device, lds_allowed[m1]);
     if (rc != ZS_OK) return rc;
     const RangeSplit rs = split_ranges((uint32_t)bv.strips * (uint32_t)bv.k_blocks, wgs);
@@ -1351,8 +1377,8 @@ int gemm_impl(const zs_desc *d, const void *blob_dev, const uint16_t *A_dev, int
         const int m = (int)((M - m0) < width ? (M - m0) : width);
         const uint16_t *Ap = A_dev + m0 * lda;
         float *Cp = out_bf16 ? reinterpret_cast<float *>(reinterpret_cast<uint16_t *>(C_dev) + m0 * ldc) : C_dev + m0 * ldc;
-#define ZS_PC_CASE(ID, MT, LW, P, R, Q) \
-    case ID: rc = launch_pc<MT, LW, P, R, Q>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, s); break;
+#define ZS_PC_CASE(ID, MT, LW, P, R, Q, F) \
+    case ID: rc = launch_pc<MT, LW, P, R, Q, F>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, s); break;
 #define ZS_CASE(ID, MT, LW, WAVES) \
     case ID: rc = launch_gemm<MT, LW, WAVES>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, scratch, out_bf16, s); break;
         switch (plan.variant) {
@@ -1362,12 +1388,12 @@ int gemm_impl(const zs_desc *d, const void *blob_dev, const uint16_t *A_dev, int
             ZS_CASE(4, 2, 512, 7)
             ZS_CASE(5, 1, 4096, 7)
             ZS_CASE(6, 2, 4096, 6)
-            ZS_PC_CASE(7, 1, 512, 7, 7, 4)
-            ZS_PC_CASE(8, 2, 512, 7, 7, 4)
-            ZS_PC_CASE(9, 2, 512, 7, 7, 8)
-            ZS_PC_CASE(10, 1, 4096, 5, 5, 4)
-            ZS_PC_CASE(11, 2, 4096, 5, 5, 4)
-            ZS_PC_CASE(12, 2, 4096, 5, 5, 8)
+            ZS_PC_CASE(7, 1, 512, 7, 7, 4, 6)
+            ZS_PC_CASE(8, 2, 512, 8, 6, 4, 6)
+            ZS_PC_CASE(9, 2, 512, 8, 6, 8, 4)
+            ZS_PC_CASE(10, 1, 4096, 5, 6, 4, 6)
+            ZS_PC_CASE(11, 2, 4096, 5, 6, 4, 6)
+            ZS_PC_CASE(12, 2, 4096, 5, 6, 8, 4)
             ZS_CASE(13, 4, 512, 7)
             ZS_CASE(14, 4, 4096, 5)
         default: rc = ZS_ERR_CONFIG;

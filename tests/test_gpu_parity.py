@@ -125,6 +125,20 @@ def test_gemm_workgroup_counts(gu):
         gu.check_gemm(W, A, config=256 * wgs)
 
 
+@pytest.mark.parametrize("law", ["gauss", "rowscale"])
+@pytest.mark.parametrize("M", [65, 97, 127, 128, 129, 193, 255, 256, 257])
+def test_gemm_shared_decode_edges(gu, M, law):
+    """Producer / consumer kernel at the edges of its consumers and launches (257: a second panel), over
+    ranges that cut strips anywhere (forced workgroup counts: one tile each, a few, all of them) and
+    hold fewer and more tiles than the ring of decoded tiles."""
+    W = inputs.gaussian_weights(320, 448, 60) if law == "gauss" else inputs.make_weights(law, 320, 448, seed=61)
+    A = inputs.activations(M, 448, 62 + M)
+    _, d = binding.zs_encode(W)
+    pick = binding.zs_gemm_pick_config(d, M)
+    for wgs in (0, 1, 3, 8):                    # 5 strips x 7 BlockTiles: 1, 35, 11 or 12, 4 or 5 to a workgroup
+        gu.check_gemm(W, A, config=pick + 256 * wgs)
+
+
 def test_gemm_shared_strips_with_and_without_scratch(gu):
     """Strips cut between workgroups: with scratch memory the partial tiles are parked there and
     summed by the last workgroup to arrive, and the whole buffer is left at zero for the next
