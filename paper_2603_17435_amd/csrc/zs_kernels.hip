@@ -527,83 +527,108 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
                 // hardware checks against the size of the area (an out-of-range read returns zero,
                 // an out-of-range write is dropped).  "Volatile": the polling reads must be repeated.
                 constexpr int kCoherent = 16 | (int)0x80000000u; // sc1 | volatile (compiler-level)
-                // kBatch = slots read at a time: what the wave's registers hold beside its own tile
-                // (from eight streaming waves on, a wave has 168 registers)
-                constexpr int kBatch = MT == 4 || (MT == 2 && WAVES > 7) ? 1 : 3;
-                constexpr uint32_t Q = kUnits / 64;
-                const uint32_t self = range_id, voff = opaque_lane() * 16;
-                const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(ws.tiles, 0, (int)ws.tiles_bytes, 0x00020000);
-                // byte offset of the slot of workgroup b for this strip: slot 0 of a workgroup holds
-                // the strip its range starts in, slot 1 the one it ends in
-                auto slot_of = [&](uint32_t b) {
-                    const uint32_t first = rs.begin(b) >= strip * k_blocks ? 0u : 1u;
-                    return uniform((2 * b + first) * kTileBytes);
-                };
-                const uint32_t mine = slot_of(self);
+                // Q_: rows of 64 float4 units (four tokens each) to exchange; BATCH: slots read at a time, what
+                // the wave's registers hold beside its own tile.  True if this workgroup finishes the strip.
+                auto exchange = [&](auto q_c, auto batch_c) {
+                    constexpr uint32_t Q = decltype(q_c)::value;
+                    constexpr int kBatch = decltype(batch_c)::value;
+                    const uint32_t self = range_id, voff = opaque_lane() * 16;
+                    const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(ws.tiles, 0, (int)ws.tiles_bytes, 0x00020000);
+                    // byte offset of the slot of workgroup b for this strip: slot 0 of a workgroup holds
+                    // the strip its range starts in, slot 1 the one it ends in
+                    auto slot_of = [&](uint32_t b) {
+                        const uint32_t first = rs.begin(b) >= strip * k_blocks ? 0u : 1u;
+                        return uniform((2 * b + first) * kTileBytes);
+                    };
+                    const uint32_t mine = slot_of(self);
 #pragma unroll
-                for (uint32_t q = 0; q < Q; ++q) {
-                    u32x4 w = __builtin_bit_cast(u32x4, v[q]);
-                    w.x = w.x ? w.x : 0x80000000u, w.y = w.y ? w.y : 0x80000000u;
-                    w.z = w.z ? w.z : 0x80000000u, w.w = w.w ? w.w : 0x80000000u;
-                    __builtin_amdgcn_raw_buffer_store_b128(w, slots, voff + q * 1024, mine, kCoherent);
-                }
-                uint32_t old = 0;
-                if (lane == 0) old = __hip_atomic_fetch_add(ws.count + b_lo, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const u32x4 zero4 = {0u, 0u, 0u, 0u};
-                bool last = false;
-                for (uint32_t b = b_lo; b <= b_hi;) {
-                    // the next kBatch contributors other than this workgroup
-                    uint32_t src[kBatch];
-                    uint32_t nb = 0; // slots in this batch (wave-uniform)
-#pragma unroll
-                    for (int i = 0; i < kBatch; ++i) {
-                        if (b == self) ++b;
-                        src[i] = slot_of(b <= b_hi ? b : self);
-                        if (b <= b_hi) ++b, ++nb;
+                    for (uint32_t q = 0; q < Q; ++q) {
+                        u32x4 w = __builtin_bit_cast(u32x4, v[q]);
+                        w.x = w.x ? w.x : 0x80000000u, w.y = w.y ? w.y : 0x80000000u;
+                        w.z = w.z ? w.z : 0x80000000u, w.w = w.w ? w.w : 0x80000000u;
+                        __builtin_amdgcn_raw_buffer_store_b128(w, slots, voff + q * 1024, mine, kCoherent);
                     }
-                    if (nb == 0) break;
-                    u32x4 t[kBatch][Q];
-                    // A parked tile arrives within a round trip of its owner's count.  The bound only
-                    // matters when the scratch contract was broken (a buffer that was not zero-filled
-                    // once, or calls overlapping on it): then this gives up and the strip is wrong.
-                    for (uint32_t polls = 0;; ++polls) {
+                    uint32_t old = 0;
+                    if (lane == 0) old = __hip_atomic_fetch_add(ws.count + b_lo, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+                    bool last = false;
+                    for (uint32_t b = b_lo; b <= b_hi;) {
+                        // the next kBatch contributors other than this workgroup
+                        uint32_t src[kBatch];
+                        uint32_t nb = 0; // slots in this batch (wave-uniform)
 #pragma unroll
-                        for (int i = 0; i < kBatch; ++i)
-                            if ((uint32_t)i < nb)
-#pragma unroll
-                                for (uint32_t q = 0; q < Q; ++q)
-                                    t[i][q] = __builtin_amdgcn_raw_buffer_load_b128(slots, voff + q * 1024, src[i], kCoherent);
-                        if (!last) { // first batch: read before this workgroup knows whether it is the last one
-                            if (uniform(old) != b_hi - b_lo) break; // somebody else will finish the strip
-                            last = true;
+                        for (int i = 0; i < kBatch; ++i) {
+                            if (b == self) ++b;
+                            src[i] = slot_of(b <= b_hi ? b : self);
+                            if (b <= b_hi) ++b, ++nb;
                         }
-                        bool missing = false;
+                        if (nb == 0) break;
+                        u32x4 t[kBatch][Q];
+                        // A parked tile arrives within a round trip of its owner's count.  The bound only
+                        // matters when the scratch contract was broken (a buffer that was not zero-filled
+                        // once, or calls overlapping on it): then this gives up and the strip is wrong.
+                        for (uint32_t polls = 0;; ++polls) {
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i)
+                                if ((uint32_t)i < nb)
+#pragma unroll
+                                    for (uint32_t q = 0; q < Q; ++q)
+                                        t[i][q] = __builtin_amdgcn_raw_buffer_load_b128(slots, voff + q * 1024, src[i], kCoherent);
+                            if (!last) { // first batch: read before this workgroup knows whether it is the last one
+                                if (uniform(old) != b_hi - b_lo) break; // somebody else will finish the strip
+                                last = true;
+                            }
+                            bool missing = false;
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i)
+                                if ((uint32_t)i < nb)
+#pragma unroll
+                                    for (uint32_t q = 0; q < Q; ++q)
+                                        missing |= t[i][q].x == 0u || t[i][q].y == 0u || t[i][q].z == 0u || t[i][q].w == 0u;
+                            if (__builtin_amdgcn_ballot_w64(missing) == 0 || polls == (1u << 15)) break;
+                            __builtin_amdgcn_s_sleep(8);
+                        }
+                        if (!last) break;
 #pragma unroll
                         for (int i = 0; i < kBatch; ++i)
                             if ((uint32_t)i < nb)
 #pragma unroll
-                                for (uint32_t q = 0; q < Q; ++q)
-                                    missing |= t[i][q].x == 0u || t[i][q].y == 0u || t[i][q].z == 0u || t[i][q].w == 0u;
-                        if (__builtin_amdgcn_ballot_w64(missing) == 0 || polls == (1u << 15)) break;
-                        __builtin_amdgcn_s_sleep(8);
+                                for (uint32_t q = 0; q < Q; ++q) {
+                                    v[q] += __builtin_bit_cast(f32x4, t[i][q]);
+                                    // (same address as the load above, same wave: stays behind it)
+                                    __builtin_amdgcn_raw_buffer_store_b128(zero4, slots, voff + q * 1024, src[i], kCoherent);
+                                }
                     }
-                    if (!last) break;
+                    if (!last) return false;
+                    // this workgroup's own slot and the counter go back to zero as well (the same
+                    // addresses as the stores above, from the same wave: they stay in that order)
 #pragma unroll
-                    for (int i = 0; i < kBatch; ++i)
-                        if ((uint32_t)i < nb)
-#pragma unroll
-                            for (uint32_t q = 0; q < Q; ++q) {
-                                v[q] += __builtin_bit_cast(f32x4, t[i][q]);
-                                // (same address as the load above, same wave: stays behind it)
-                                __builtin_amdgcn_raw_buffer_store_b128(zero4, slots, voff + q * 1024, src[i], kCoherent);
-                            }
+                    for (uint32_t q = 0; q < Q; ++q) __builtin_amdgcn_raw_buffer_store_b128(zero4, slots, voff + q * 1024, mine, kCoherent);
+                    if (lane == 0) __hip_atomic_store(ws.count + b_lo, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return true;
+                };
+                constexpr uint32_t kRows = kUnits / 64;
+                // A last contributor's round trips, one after the other, are what a small layer's call ends
+                // with.  Beyond four contributors to a strip as many partial tiles are read at a time as the
+                // registers hold, and only the tokens there are go through scratch memory (with up to four of
+                // the sixteen a quarter of a slot).  1024 x 4096, 16 contributors, whole slots three at a
+                // time / as here: 14.6 / 10.2 us at 1 token, 14.8 / 11.5 at 7, 14.7 / 13.5 at 16.  With four or fewer one
+                // batch of three is enough and its addresses are sooner formed (4096 x 4096, 1 token: 13.5 us, with
+                // batches of sixteen 13.9).  Three is also the batch at 32 tokens with up to seven streaming
+                // waves (beyond, a wave has 168 registers).
+                bool finished;
+                if (MT == 1 && b_hi - b_lo > 3) {
+                    if (M <= 4)
+                        finished = exchange(std::integral_constant<uint32_t, 1>{}, std::integral_constant<int, 16>{});
+                    else if (M <= 8)
+                        finished = exchange(std::integral_constant<uint32_t, 2>{}, std::integral_constant<int, 8>{});
+                    else
+                        finished = exchange(std::integral_constant<uint32_t, 4>{}, std::integral_constant<int, MT == 1 ? 5 : 1>{});
+                } else {
+                    finished = exchange(std::integral_constant<uint32_t, kRows>{},
+                                        std::integral_constant<int, (MT == 4 || (MT == 2 && WAVES > 7) ? 1 : 3)>{});
                 }
-                if (!last) continue;
-                // this workgroup's own slot and the counter go back to zero as well (the same
-                // addresses as the stores above, from the same wave: they stay in that order)
-#pragma unroll
-                for (uint32_t q = 0; q < Q; ++q) __builtin_amdgcn_raw_buffer_store_b128(zero4, slots, voff + q * 1024, mine, kCoherent);
-                if (lane == 0) __hip_atomic_store(ws.count + b_lo, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!finished) continue;
             }
             const uint32_t lane_c = opaque_lane();
             if (ws.out_bf16) { // the same unit as four BF16: 8 bytes at the same element offset

@@ -125,6 +125,25 @@ def test_gemm_workgroup_counts(gu):
         gu.check_gemm(W, A, config=256 * wgs)
 
 
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("contributors", [2, 6, 9, 10, 17, 18, 40])
+def test_gemm_exchange_batches(gu, contributors, M):
+    """One strip summed from several workgroups, around the number of partial tiles that are read at a
+    time (5, 8 or 16 by the number of tokens); the scratch buffer is zero again afterwards."""
+    import torch
+    K = 64 * contributors                       # one BlockTile, so one workgroup, per contributor
+    W, A = inputs.gaussian_weights(64, K, 70), inputs.activations(M, K, 71 + M)
+    C_ref, S = oracle.gemm(A, W)
+    blob, d = binding.zs_encode(W)
+    dev, a = gu.upload_blob(blob), torch.from_numpy(A.view(np.int16)).cuda()
+    ws = torch.zeros(max(binding.zs_gemm_workspace(d, M), 256), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        c = torch.full((M, 64), float("nan"), dtype=torch.float32, device="cuda")
+        binding.zs_gemm(d, dev, a, c, M, workspace_dev=ws, workspace_bytes=ws.numel())
+        gu.assert_gemm_matches(c.cpu().numpy(), C_ref, S)
+        assert not ws.any()
+
+
 @pytest.mark.parametrize("law", ["gauss", "rowscale"])
 @pytest.mark.parametrize("M", [65, 97, 127, 128, 129, 193, 255, 256, 257])
 def test_gemm_shared_decode_edges(gu, M, law):
