@@ -25,6 +25,20 @@ def test_decompress_bit_exact_small(gu, kind, N, K):
     assert np.array_equal(out, W)
 
 
+@pytest.mark.parametrize("pad", [0, 8, 40, 64])
+def test_decompress_rows_and_padding(gu, pad):
+    """Every element differs from its neighbours in row and column (a swapped lane, row or half shows),
+    and the columns between the rows stay as they were."""
+    import torch
+    N, K = 320, 192
+    W = (np.arange(N, dtype=np.uint32)[:, None] * 131 + np.arange(K, dtype=np.uint32) * 7 + 0x3A00).astype(np.uint16)
+    blob, d = binding.zs_encode(W)
+    out = torch.full((N, K + pad), 0x5A5A, dtype=torch.int16, device="cuda")
+    binding.zs_decompress(d, gu.upload_blob(blob), out, ldw=K + pad)
+    got = out.cpu().numpy().view(np.uint16)
+    assert np.array_equal(got[:, :K], W) and (got[:, K:] == 0x5A5A).all()
+
+
 def test_decompress_all_bit_patterns(gu):
     W = np.random.default_rng(0).permutation(np.arange(65536, dtype=np.uint16)).reshape(256, 256)
     assert np.array_equal(gu.gpu_decompress(W), W)
