@@ -3,7 +3,7 @@
 //
 //   1. sample_kernel  predicts the exponent window from 16 K of the weights
 //   2. hist_kernel    exponent histogram of all weights, and the in-window elements of every
-//                     BlockTile under the predicted window (parked in the offset section)
+//                     BlockTile under the predicted window (parked where the bit-planes will be)
 //   3. recount_kernel repeats the counts when the window of the full histogram is another one
 //                     (near ties only); otherwise it ends at once
 //   4. scan_kernel    segment offsets = prefix sums of the padded segment sizes, totals
@@ -170,7 +170,7 @@ __device__ __forceinline__ uint32_t fallbacks_of(const u32x4 (&v)[ZS_TT_PER_BT],
 // workgroup and bin in use.
 constexpr uint32_t kHistWaves = 16;
 __global__ __launch_bounds__(64 * kHistWaves) void hist_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
-                                                               unsigned long long *hist, const Totals *totals, uint32_t *offsets)
+                                                               unsigned long long *hist, const Totals *totals, uint32_t *counts)
 {
     __shared__ __attribute__((aligned(16))) uint8_t bins[256 * kCopies * 4];
     for (uint32_t i = threadIdx.x; i < 256 * kCopies; i += blockDim.x) reinterpret_cast<uint32_t *>(bins)[i] = 0;
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_kernel(const uint16_t *W
 #pragma unroll
             for (int c = 0; c < 4; ++c) count_pair(bins, v[tt][c], copy4);
         const uint32_t f = fallbacks_of(v, lo2);
-        if (lane == 0) offsets[2 * bt] = ZS_BT_ELEMS - f;
+        if (lane == 0) counts[bt] = ZS_BT_ELEMS - f;
     }
     __syncthreads();
     if (threadIdx.x < 256) {
@@ -197,84 +197,93 @@ __global__ __launch_bounds__(64 * kHistWaves) void hist_kernel(const uint16_t *W
 }
 
 // The counts again, under the window of the full histogram, when it is not the predicted one.
-__global__ __launch_bounds__(256) void recount_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
-                                                      const unsigned long long *hist, const Totals *totals, uint32_t *offsets)
+__global__ __launch_bounds__(64 * kHistWaves) void recount_kernel(const uint16_t *W, int64_t ldw, uint32_t k_blocks, uint32_t n_bt,
+                                                      const unsigned long long *hist, const Totals *totals, uint32_t *counts)
 {
     __shared__ unsigned long long sums[256];
     const Window w = pick_window(hist, sums);
     if (w.lo == totals->predicted_lo) return;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint64_t bt = (uint64_t)blockIdx.x * 4 + wave; bt < n_bt; bt += (uint64_t)gridDim.x * 4) {
+    for (uint64_t bt = (uint64_t)blockIdx.x * kHistWaves + wave; bt < n_bt; bt += (uint64_t)gridDim.x * kHistWaves) {
         const uint16_t *tile = tile_at(W, ldw, k_blocks, (uint32_t)bt);
         u32x4 v[ZS_TT_PER_BT];
 #pragma unroll
         for (int tt = 0; tt < ZS_TT_PER_BT; ++tt) v[tt] = load_row(tile, ldw, tt, lane);
         const uint32_t f = fallbacks_of(v, w.lo * 0x00010001u);
-        if (lane == 0) offsets[2 * bt] = ZS_BT_ELEMS - f;
+        if (lane == 0) counts[bt] = ZS_BT_ELEMS - f;
     }
 }
 
-// One workgroup: offsets[bt] = {sum of H units before bt, sum of L units before bt}, in place over
-// the parked counts; offsets[n_bt], the window and the totals at the end.  A thread takes eight
-// consecutive BlockTiles, so 8192 share one exchange between the waves (28672 BlockTiles: 16 us; one
-// BlockTile per thread and a scan through LDS took 140 us).  (Unit sums stay below
-// 2^32: the host refuses larger matrices.)
-__global__ __launch_bounds__(1024) void scan_kernel(uint32_t *offsets, uint32_t n_bt, const unsigned long long *hist, Totals *totals)
+// offsets[bt] = {sum of H units before bt, sum of L units before bt}; offsets[n_bt], the window and the
+// totals at the end.  A workgroup takes per_wg BlockTiles (a multiple of kScanRound) and adds up the
+// counts of all BlockTiles before them itself: reading them again (4 bytes a BlockTile, from L2) costs less
+// than passing sums from one workgroup to the next.  Bound by latency: one workgroup that took the BlockTiles in
+// turn needed 16 us for the 28672 of a 28672 x 4096 layer; with seven the whole call went from 178 to 171 us.
+// (Unit sums stay below 2^32: the host
+// refuses larger matrices.)
+constexpr uint32_t kScanRound = 4096, kScanWgs = 64;
+__global__ __launch_bounds__(1024) void scan_kernel(const uint32_t *counts, uint32_t *offsets, uint32_t n_bt, uint32_t per_wg,
+                                                    const unsigned long long *hist, Totals *totals)
 {
     __shared__ unsigned long long sums[256];
     __shared__ uint32_t wave_h[2][16], wave_l[2][16], max_h, max_l;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    if (t == 0) max_h = 0, max_l = 0;
-    uint32_t run_h = 0, run_l = 0, mh = 0, ml = 0, par = 0;
-    auto live_at = [&](uint64_t bt0) { return bt0 >= n_bt ? 0u : n_bt - bt0 < 8 ? (uint32_t)(n_bt - bt0) : 8u; };
-    u32x4 q[4]; // the counts of the round (even words)
-    auto fetch = [&](uint64_t bt0) {
-        if (live_at(bt0) == 8) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const u32x4 *>(offsets + 2 * bt0 + 4 * i);
-        } else {
-#pragma unroll
-            for (uint32_t i = 0; i < 8; ++i) q[i / 2][2 * (i & 1)] = i < live_at(bt0) ? offsets[2 * (bt0 + i)] : 0u;
-        }
+    const uint32_t first = blockIdx.x * per_wg, end = n_bt - first < per_wg ? n_bt : first + per_wg;
+    uint32_t mh = 0, ml = 0;
+    auto units = [&](uint32_t nh, uint32_t &hu, uint32_t &lu) {
+        hu = (nh + 15u) / 16u, lu = (2u * (ZS_BT_ELEMS - nh) + 15u) / 16u;
+        mh = max(mh, hu), ml = max(ml, lu);
     };
-    fetch(8 * t);
-    const Window w = pick_window(hist, sums);
-    for (uint64_t base = 0; base < n_bt; base += 8192, par ^= 1) {
-        const uint64_t bt0 = base + 8 * t;
-        const uint32_t live = live_at(bt0);
-        uint32_t hu[8], lu[8], h = 0, l = 0;
+    // ---- what lies before this workgroup's BlockTiles (first is a multiple of kScanRound)
+    uint32_t before_h = 0, before_l = 0;
+#pragma unroll 4
+    for (uint32_t bt = 4 * t; bt < first; bt += kScanRound) {
+        const u32x4 q = *reinterpret_cast<const u32x4 *>(counts + bt);
 #pragma unroll
-        for (uint32_t i = 0; i < 8; ++i) {
-            const uint32_t nh = q[i / 2][2 * (i & 1)];
-            hu[i] = i < live ? (nh + 15u) / 16u : 0u, lu[i] = i < live ? (2u * (ZS_BT_ELEMS - nh) + 15u) / 16u : 0u;
-            h += hu[i], l += lu[i];
-            mh = max(mh, hu[i]), ml = max(ml, lu[i]);
+        for (int i = 0; i < 4; ++i) {
+            uint32_t hu, lu;
+            units(q[i], hu, lu);
+            before_h += hu, before_l += lu;
         }
-        fetch(bt0 + 8192); // in flight over the exchange between the waves
+    }
+    uint32_t run_h = 0, run_l = 0;
+    // Sums of h and l over the threads before this one, on top of run_h and run_l, which move on by the
+    // sums over all.  (Two sets of wave sums by turns, so one barrier is enough.)
+    auto exclusive = [&](uint32_t par, uint32_t h, uint32_t l, uint32_t &at_h, uint32_t &at_l) {
         const uint32_t inc_h = wave_inclusive_scan(h), inc_l = wave_inclusive_scan(l);
         if (lane == 63) wave_h[par][wave] = inc_h, wave_l[par][wave] = inc_l;
-        __syncthreads(); // (two sets of sums by turns: the next round writes the other one)
-        uint32_t at_h = run_h + inc_h - h, at_l = run_l + inc_l - l;
+        __syncthreads();
+        at_h = run_h + inc_h - h, at_l = run_l + inc_l - l;
         for (uint32_t i = 0; i < 16; ++i) {
             const uint32_t sh = wave_h[par][i], sl = wave_l[par][i];
             at_h += i < wave ? sh : 0u, at_l += i < wave ? sl : 0u;
             run_h += sh, run_l += sl;
         }
+    };
+    uint32_t at_h, at_l, par = 1;
+    exclusive(0, before_h, before_l, at_h, at_l);
+    for (uint32_t base = first; base < end; base += kScanRound, par ^= 1) {
+        const uint32_t bt0 = base + 4 * t, live = bt0 >= end ? 0u : min(end - bt0, 4u);
+        u32x4 q = {0u, 0u, 0u, 0u};
+        if (live == 4) q = *reinterpret_cast<const u32x4 *>(counts + bt0);
+        else
+            for (uint32_t i = 0; i < live; ++i) q[i] = counts[bt0 + i];
+        uint32_t hu[4] = {0u, 0u, 0u, 0u}, lu[4] = {0u, 0u, 0u, 0u}, h = 0, l = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            u32x4 o;
-            o.x = at_h, o.y = at_l;
-            at_h += hu[2 * i], at_l += lu[2 * i];
-            o.z = at_h, o.w = at_l;
-            at_h += hu[2 * i + 1], at_l += lu[2 * i + 1];
-            if (live == 8) *reinterpret_cast<u32x4 *>(offsets + 2 * bt0 + 4 * i) = o;
-            else {
-                if (2 * i < (int)live) offsets[2 * (bt0 + 2 * i)] = o.x, offsets[2 * (bt0 + 2 * i) + 1] = o.y;
-                if (2 * i + 1 < (int)live) offsets[2 * (bt0 + 2 * i) + 2] = o.z, offsets[2 * (bt0 + 2 * i) + 3] = o.w;
-            }
+        for (uint32_t i = 0; i < 4; ++i) {
+            if (i < live) units(q[i], hu[i], lu[i]);
+            h += hu[i], l += lu[i];
+        }
+        exclusive(par, h, l, at_h, at_l);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            if (i < live) *reinterpret_cast<u32x2 *>(offsets + 2 * ((size_t)bt0 + i)) = u32x2{at_h, at_l};
+            at_h += hu[i], at_l += lu[i];
         }
     }
-    __syncthreads();
+    if (end != n_bt) return;
+    if (t == 0) max_h = 0, max_l = 0;
+    const Window w = pick_window(hist, sums); // (its barriers are also those of the maxima)
     atomicMax(&max_h, mh);
     atomicMax(&max_l, ml);
     __syncthreads();
@@ -433,16 +442,20 @@ extern "C" int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int
     const uint64_t off_offsets = align_up((uint64_t)n_bt * ZS_BT_BITMAP_BYTES, ZS_SECTION_ALIGN);
     const uint64_t off_H = align_up(off_offsets + ((uint64_t)n_bt + 1) * 8, ZS_SECTION_ALIGN);
     uint32_t *offsets_dev = reinterpret_cast<uint32_t *>(blob + off_offsets);
+    // the counts of the BlockTiles lie where the bit-planes will be: pack_kernel writes those last
+    uint32_t *counts_dev = reinterpret_cast<uint32_t *>(blob + off_bitmaps);
 
     // ---- window and counts (Algorithm 1, phase I), segment offsets, then the tiles (phase II)
     const uint32_t wgs = (uint32_t)(2 * zs_compute_units());
     auto at_most = [](uint64_t want, uint32_t limit) { return dim3((unsigned)(want < limit ? want : limit)); };
     hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(1024), 0, s, W_dev, N, K, ldw, hist_dev, totals_dev);
     hipLaunchKernelGGL(hist_kernel, at_most((n_bt + kHistWaves - 1) / kHistWaves, wgs), dim3(64 * kHistWaves), 0, s, W_dev, ldw, k_blocks,
-                       n_bt, hist_dev, totals_dev, offsets_dev);
-    hipLaunchKernelGGL(recount_kernel, at_most((n_bt + 3) / 4, 4 * wgs), dim3(256), 0, s, W_dev, ldw, k_blocks, n_bt, hist_dev, totals_dev,
-                       offsets_dev);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, offsets_dev, n_bt, hist_dev, totals_dev);
+                       n_bt, hist_dev, totals_dev, counts_dev);
+    hipLaunchKernelGGL(recount_kernel, at_most((n_bt + kHistWaves - 1) / kHistWaves, wgs), dim3(64 * kHistWaves), 0, s, W_dev, ldw, k_blocks,
+                       n_bt, hist_dev, totals_dev, counts_dev);
+    const uint32_t per_wg = kScanRound * ((n_bt + kScanRound * kScanWgs - 1) / (kScanRound * kScanWgs));
+    hipLaunchKernelGGL(scan_kernel, dim3((n_bt + per_wg - 1) / per_wg), dim3(1024), 0, s, counts_dev, offsets_dev, n_bt, per_wg, hist_dev,
+                       totals_dev);
     hipLaunchKernelGGL(pack_kernel, dim3((n_bt + 3) / 4 + 1), dim3(256), 0, s, W_dev, ldw, k_blocks, n_bt, totals_dev, blob,
                        (uint64_t)blob_cap, offsets_dev, off_offsets, off_H);
     Totals tot;

@@ -411,6 +411,21 @@ def test_error_paths(gu):
         binding.zs_decompress(d, dev, None)
 
 
+@pytest.mark.parametrize("strips,k_blocks", [(63, 65), (64, 64), (17, 241), (3, 2731)])
+def test_encode_device_scan_workgroups(strips, k_blocks):
+    """Numbers of BlockTiles around a workgroup's share of the prefix sum: 4095, 4096, 4097, 8193."""
+    import torch
+    N, K = 64 * strips, 64 * k_blocks
+    W = inputs.make_weights("student_t", N, K, seed=92)
+    blob, d = binding.zs_encode(W)
+    cap = binding.zs_encode_bound(N, K)
+    out = torch.full((cap,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = torch.full((binding.ZS_ENCODE_WORKSPACE_BYTES,), 0xFF, dtype=torch.uint8, device="cuda")
+    d_dev = binding.zs_encode_device(torch.from_numpy(W.view(np.int16)).cuda(), N, K, out, cap, ws)
+    assert desc_fields(d_dev) == desc_fields(d)
+    assert np.array_equal(out.cpu().numpy()[:d.total_bytes], blob)
+
+
 def tied_windows(N, K):
     """Exponents 100..115 in equal shares: every window inside covers the same, the smallest start
     wins, and a prediction from a part of the weights has no reason to agree."""
