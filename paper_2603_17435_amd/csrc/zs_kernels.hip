@@ -1202,11 +1202,12 @@ struct GemmVariant {
 
 // id = index + 1.  The first entry of each (tokens, lw, kernel) triple is the default for it.
 // Names: m<tokens per launch>_l<0: 512-byte, 4: 4 KB L window>_w<streaming waves> for
-// gemm_stream_kernel, p<tokens per launch>_l<..>_w<producer waves> for gemm_pc_kernel.
+// gemm_stream_kernel, p<tokens per launch>_l<..>_w<producer waves> for gemm_pc_kernel.  Callers look
+// configurations up by name, so a name stays when its kernel changes: 8 and 9 run eight producers now.
 const GemmVariant kVariants[] = {
     {"m16_l0_w11", 1, 512, 11, 0}, {"m16_l0_w8", 1, 512, 8, 0},   {"m32_l0_w10", 2, 512, 10, 0},
     {"m32_l0_w7", 2, 512, 7, 0},   {"m16_l4_w7", 1, 4096, 7, 0},  {"m32_l4_w6", 2, 4096, 6, 0},
-    {"p64_l0_w7", 1, 512, 7, 4},   {"p128_l0_w8", 2, 512, 8, 4},  {"p256_l0_w8", 2, 512, 8, 8},
+    {"p64_l0_w7", 1, 512, 7, 4},   {"p128_l0_w7", 2, 512, 8, 4},  {"p256_l0_w7", 2, 512, 8, 8},
     {"p64_l4_w5", 1, 4096, 5, 4},  {"p128_l4_w5", 2, 4096, 5, 4}, {"p256_l4_w5", 2, 4096, 5, 8},
     {"m64_l0_w7", 4, 512, 7, 0},   {"m64_l4_w5", 4, 4096, 5, 0},
 };

@@ -90,6 +90,10 @@ def test_config_table():
     cfgs = binding.zs_gemm_configs()
     assert len(cfgs) == binding.lib().zs_gemm_num_configs() >= 3
     assert binding.lib().zs_gemm_config_name(0) is None
+    # names are how callers find a configuration: they stay, whatever runs behind them
+    assert [cfgs[i] for i in sorted(cfgs)] == ["m16_l0_w11", "m16_l0_w8", "m32_l0_w10", "m32_l0_w7", "m16_l4_w7", "m32_l4_w6",
+                                               "p64_l0_w7", "p128_l0_w7", "p256_l0_w7", "p64_l4_w5", "p128_l4_w5", "p256_l4_w5",
+                                               "m64_l0_w7", "m64_l4_w5"]
     _, d = binding.zs_encode(np.zeros((64, 64), dtype=np.uint16))
     assert binding.zs_gemm_pick_config(d, 1) in cfgs and binding.zs_gemm_pick_config(d, 32) in cfgs
 
