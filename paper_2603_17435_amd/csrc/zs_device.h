@@ -353,7 +353,7 @@ __device__ __forceinline__ RowFallbacks load_fallbacks(uint32_t tab, const TileL
 // from global memory, one at a time in a per-lane loop, when the L segment did not fit the staged
 // window.  kLoop takes the third and later fallbacks of a row one at a time as well, kMany takes
 // them register by register without a branch (load_fallbacks).  Which of the two a matrix gets is
-// its fallback density (decode_block_tile): a loop costs little where a wave finds one such row now and
+// its fallback density and spread (careful_loop): a loop costs little where a wave finds one such row now and
 // then, and up to six rounds of an LDS read and an insertion where it finds many.  Measured at 16
 // tokens, kLoop / kMany: 4096 x 14336, a third of the weights outside the window, 74.7 / 32.8 us;
 // 28672 x 4096 N(0, 0.02), 2 % of them, 40.0 / 40.6 us.

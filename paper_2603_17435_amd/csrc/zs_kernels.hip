@@ -35,9 +35,6 @@ struct Slot {
     static constexpr uint32_t kBytes = kL + LW + 64;
     static constexpr int kLChunks = (LW + 1023) / 1024;
     static constexpr int kLoads = 2 + 4 + kLChunks; // LDS-direct instructions per BlockTile
-    // A matrix with few fallbacks gets the short window (pick_l_window): then rows with more than two
-    // of them are rare and the loop is the better one, else they are the rule.
-    static constexpr Fallbacks kCareful = LW == 512 ? kLoop : kMany;
     // what the LDS-direct loads of a tile can write: 1536 bytes of bit-planes, four 1 KB pieces of
     // H, kLChunks pieces of L (one 512-byte piece for LW = 512); all of it lies inside the slot
     static_assert(kPlanes + ZS_BT_BITMAP_BYTES <= kH && kH + 4 * 1024 <= kL, "sections of a slot overlap");
@@ -213,7 +210,7 @@ __device__ __forceinline__ StagedL stage_tile(const BlobView &bv, const TileRef 
 // and writes 399 MB in 77.7 us, 5.1 TB/s, the rate of a device copy (5.2); with half lines it
 // was 98.8 us.  4096 x 14336: 37.7 -> 33.9 us.  Without the non-temporal hint 83 and 44 us.
 // --------------------------------------------------------------------------------------
-template <int LW, int DEPTH, int WAVES, bool BASE_M1>
+template <int LW, int DEPTH, int WAVES, bool BASE_M1, Fallbacks CAREFUL>
 __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uint16_t *out, int64_t ldw)
 {
     using S = Slot<LW>;
@@ -260,7 +257,7 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
         // other rows 8 .. 15.
         uint16_t *dst = out + ((int64_t)strip * 64 + row) * ldw + (int64_t)kb * 64 + col;
         u32x4 left[4]; // the TensorCoreTiles of the first k half, until their neighbours are decoded
-        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
+        decode_block_tile<BASE_M1, 0, 0, CAREFUL>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
                                          [&](int tt, const u32x4 &w) {
                                              if (tt < 4) {
                                                  left[tt] = w;
@@ -374,7 +371,7 @@ struct RangeSplit {
     }
 };
 
-template <int MT, int LW, int WAVES, bool BASE_M1>
+template <int MT, int LW, int WAVES, bool BASE_M1, Fallbacks CAREFUL>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView bv, const uint16_t *A, int64_t lda,
                                                                   float *C, int64_t ldc, int M, SharedSums ws,
                                                                   RangeSplit rs)
@@ -786,7 +783,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
             for (int j = 0; j < MT; ++j) {
                 bop[kh][j] = __builtin_bit_cast(bf16x8, bfrag[kh][j]);
             }
-        decode_block_tile<BASE_M1, CUR * S::kBytes, kLX, S::kCareful>(tab, pa0, h0, h_base, l_lane0, fs, [&](int tt, const u32x4 &w) {
+        decode_block_tile<BASE_M1, CUR * S::kBytes, kLX, CAREFUL>(tab, pa0, h0, h_base, l_lane0, fs, [&](int tt, const u32x4 &w) {
             const bf16x8 wop = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
             for (int j = 0; j < MT; ++j)
@@ -857,7 +854,7 @@ __device__ __forceinline__ void accumulators_done(f32x4 (&acc)[4][MT])
 }
 enum : uint32_t { kPcNext = 0, kPcReady = 64, kPcConsumed = 128, kPcCtlBytes = 192, kDenseBytes = 8192 };
 
-template <int MT, int LW, int P, int R, int Q, int F, bool BASE_M1>
+template <int MT, int LW, int P, int R, int Q, int F, bool BASE_M1, Fallbacks CAREFUL>
 __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, const uint16_t *A, int64_t lda,
                                                                           float *C, int64_t ldc, int M, int q_active,
                                                                           RangeSplit rs)
@@ -1071,7 +1068,7 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         index_half<true>(h_base, h0);
         const FallbackSource fs = {slot + S::kL, reinterpret_cast<const uint16_t *>(s_l[CUR].l), s_l[CUR].big != 0};
         u32x4 dec[8];
-        decode_block_tile<BASE_M1, 0, 0, S::kCareful>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
+        decode_block_tile<BASE_M1, 0, 0, CAREFUL>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
                                          [&](int tt, const u32x4 &w) { dec[tt] = w; });
 
         // the dense slot must have been read by every consumer before it is overwritten
@@ -1192,6 +1189,21 @@ int pick_l_window(const zs_desc *d)
     return want <= 512 ? 512 : 4096;
 }
 
+// How a matrix's rows with more than two fallbacks are decoded (enum Fallbacks).  With the short L
+// window they are rare: one at a time.  With the long one they are the rule, unless the fallbacks are
+// few and lie evenly, so that three in a row of eight stay the exception: at most one weight in 18,
+// and no BlockTile with more than one and a half times the average (L segments in bytes).  Measured
+// with a share of the weights outside the window, 4096 x 14336, 16 tokens, kLoop / kMany: anywhere in the
+// matrix 4.2 % 25.9 / 25.9 us, 5 % 28.9 / 29.9, 5.5 % 30.1 / 30.6, 6 % 31.3 / 31.0, 8 % 34.5 / 31.7; 5 % of
+// them in a tenth of the rows (2.8 times the average in the fullest BlockTile) 59.3 / 31.3.  (Where base_exp
+// is -1 the long window has kMany alone: no such matrix is worth another kernel.)
+bool careful_loop(const zs_desc *d)
+{
+    const uint64_t n_bt = (uint64_t)(d->N / 64) * (uint64_t)(d->K / 64);
+    return pick_l_window(d) == 512 ||
+           (18 * d->n_fallback <= n_bt * ZS_BT_ELEMS && d->max_l_units * 16ull * n_bt <= 3 * d->n_fallback);
+}
+
 struct GemmVariant {
     const char *name;
     int mt, lw, waves;
@@ -1246,16 +1258,19 @@ size_t shared_sums_bytes(uint32_t wgs, int mt) { return kScratchHeaderBytes + (s
 
 template <int MT, int LW, int WAVES>
 int launch_gemm(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int64_t ldc, int M, uint32_t wgs,
-                int device, void *scratch, bool out_bf16, hipStream_t s)
+                int device, bool loop, void *scratch, bool out_bf16, hipStream_t s)
 {
     using S = Slot<LW>;
     constexpr uint32_t lds = StreamLds<MT, LW, WAVES>::kTotal;
     static_assert(lds <= kMaxLds, "variant does not fit the 160 KB of LDS");
     static_assert(S::kLoads < 64, "vmcnt cannot count that many loads");
-    static std::atomic<uint64_t> lds_allowed[2];
-    const bool m1 = bv.base_exp < 0;
-    auto kern = m1 ? gemm_stream_kernel<MT, LW, WAVES, true> : gemm_stream_kernel<MT, LW, WAVES, false>;
-    int rc = allow_big_lds(kern, lds, device, lds_allowed[m1]);
+    static std::atomic<uint64_t> lds_allowed[3];
+    constexpr Fallbacks kRows = LW == 512 ? kLoop : kMany; // careful_loop is about the long window
+    const int site = bv.base_exp < 0 ? 0 : loop ? 1 : 2;
+    auto kern = site == 0   ? gemm_stream_kernel<MT, LW, WAVES, true, kRows>
+                : site == 1 ? gemm_stream_kernel<MT, LW, WAVES, false, kLoop>
+                            : gemm_stream_kernel<MT, LW, WAVES, false, kRows>;
+    int rc = allow_big_lds(kern, lds, device, lds_allowed[site]);
     if (rc != ZS_OK) return rc;
     const RangeSplit rs = split_ranges((uint32_t)bv.strips * (uint32_t)bv.k_blocks, wgs);
     SharedSums ws = {nullptr, nullptr, kSumCleared, out_bf16 ? 1u : 0u, 0u};
@@ -1274,16 +1289,19 @@ int launch_gemm(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, in
 
 template <int MT, int LW, int P, int R, int Q, int F>
 int launch_pc(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int64_t ldc, int M, uint32_t wgs,
-              int device, hipStream_t s)
+              int device, bool loop, hipStream_t s)
 {
     using S = Slot<LW>;
     constexpr uint32_t lds = kTableBytes + kPcCtlBytes + R * kDenseBytes + P * 2 * S::kBytes;
     static_assert(lds <= kMaxLds, "variant does not fit the 160 KB of LDS");
     static_assert(S::kLoads < 64, "vmcnt cannot count that many loads");
-    static std::atomic<uint64_t> lds_allowed[2];
-    const bool m1 = bv.base_exp < 0;
-    auto kern = m1 ? gemm_pc_kernel<MT, LW, P, R, Q, F, true> : gemm_pc_kernel<MT, LW, P, R, Q, F, false>;
-    int rc = allow_big_lds(kern, lds, device, lds_allowed[m1]);
+    static std::atomic<uint64_t> lds_allowed[3];
+    constexpr Fallbacks kRows = LW == 512 ? kLoop : kMany;
+    const int site = bv.base_exp < 0 ? 0 : loop ? 1 : 2;
+    auto kern = site == 0   ? gemm_pc_kernel<MT, LW, P, R, Q, F, true, kRows>
+                : site == 1 ? gemm_pc_kernel<MT, LW, P, R, Q, F, false, kLoop>
+                            : gemm_pc_kernel<MT, LW, P, R, Q, F, false, kRows>;
+    int rc = allow_big_lds(kern, lds, device, lds_allowed[site]);
     if (rc != ZS_OK) return rc;
     const RangeSplit rs = split_ranges((uint32_t)bv.strips * (uint32_t)bv.k_blocks, wgs);
     clear_shared_strips(bv, C, ldc, M, rs, s);
@@ -1330,7 +1348,7 @@ extern "C" int zs_decompress(const zs_desc *d, const void *blob_dev, uint16_t *W
     DeviceInfo di;
     if ((rc = device_info(&di)) != ZS_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    static std::atomic<uint64_t> lds_allowed[4];
+    static std::atomic<uint64_t> lds_allowed[5];
     auto launch = [&](auto kern, uint32_t lds, int waves, int site) {
         int r = allow_big_lds(kern, lds, di.id, lds_allowed[site]);
         if (r != ZS_OK) return r;
@@ -1345,12 +1363,13 @@ extern "C" int zs_decompress(const zs_desc *d, const void *blob_dev, uint16_t *W
         // 11 x 2, 10 x 2, 6 x 4 and 5 x 4: 2 to 10 % faster on the 8B shapes)
         constexpr uint32_t lds = kTableBytes + 8 * 3 * Slot<512>::kBytes;
         static_assert(lds <= kMaxLds, "variant does not fit the 160 KB of LDS");
-        return m1 ? launch(decompress_kernel<512, 3, 8, true>, lds, 8, 0)
-                  : launch(decompress_kernel<512, 3, 8, false>, lds, 8, 1);
+        return m1 ? launch(decompress_kernel<512, 3, 8, true, kLoop>, lds, 8, 0)
+                  : launch(decompress_kernel<512, 3, 8, false, kLoop>, lds, 8, 1);
     }
     constexpr uint32_t lds = kTableBytes + 7 * 2 * Slot<4096>::kBytes;
-    return m1 ? launch(decompress_kernel<4096, 2, 7, true>, lds, 7, 2)
-              : launch(decompress_kernel<4096, 2, 7, false>, lds, 7, 3);
+    return m1                ? launch(decompress_kernel<4096, 2, 7, true, kMany>, lds, 7, 2)
+           : careful_loop(d) ? launch(decompress_kernel<4096, 2, 7, false, kLoop>, lds, 7, 3)
+                             : launch(decompress_kernel<4096, 2, 7, false, kMany>, lds, 7, 4);
 }
 
 extern "C" int zs_compute_units(void) { return cus_or_default(); }
@@ -1420,14 +1439,15 @@ int gemm_impl(const zs_desc *d, const void *blob_dev, const uint16_t *A_dev, int
     if (out_bf16 && !scratch) return ZS_ERR_SIZE;
     // tokens beyond the variant's width are handled in successive column panels
     const int width = v.tokens();
+    const bool loop = careful_loop(d);
     for (int64_t m0 = 0; m0 < M; m0 += width) {
         const int m = (int)((M - m0) < width ? (M - m0) : width);
         const uint16_t *Ap = A_dev + m0 * lda;
         float *Cp = out_bf16 ? reinterpret_cast<float *>(reinterpret_cast<uint16_t *>(C_dev) + m0 * ldc) : C_dev + m0 * ldc;
 #define ZS_PC_CASE(ID, MT, LW, P, R, Q, F) \
-    case ID: rc = launch_pc<MT, LW, P, R, Q, F>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, s); break;
+    case ID: rc = launch_pc<MT, LW, P, R, Q, F>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, loop, s); break;
 #define ZS_CASE(ID, MT, LW, WAVES) \
-    case ID: rc = launch_gemm<MT, LW, WAVES>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, scratch, out_bf16, s); break;
+    case ID: rc = launch_gemm<MT, LW, WAVES>(bv, Ap, lda, Cp, ldc, m, wgs, di.id, loop, scratch, out_bf16, s); break;
         switch (plan.variant) {
             ZS_CASE(1, 1, 512, 11)
             ZS_CASE(2, 1, 512, 8)

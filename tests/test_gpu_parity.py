@@ -104,6 +104,27 @@ def test_rows_with_many_fallbacks(gu, per_row):
         gu.check_gemm(W, inputs.activations(M, 448, 52 + M))
 
 
+@pytest.mark.parametrize("share,rows,loop", [(0.05, 1.0, True), (0.0545, 1.0, True), (0.056, 1.0, False), (0.05, 0.1, False)])
+def test_careful_decoder_choice(gu, share, rows, loop):
+    """The long L window with few fallbacks that lie evenly (rows of three and more one at a time) and
+    with more of them, or with as many in a tenth of the rows (register by register)."""
+    rng = np.random.default_rng(54)
+    N, K = 1024, 448
+    W = inputs.gaussian_weights(N, K, 55) & 0x807F | 0x3F80      # one exponent, so nothing else falls out
+    chosen = rng.permutation(N)[:int(N * rows)]
+    pick = np.zeros((N, K), dtype=bool)
+    flat = rng.permutation(chosen.size * K)[:round(N * K * share)]
+    pick[chosen[flat // K], flat % K] = True
+    W = np.where(pick, (W & 0x807F) | (rng.integers(1, 60, W.shape) << 7), W).astype(np.uint16)
+    _, d = binding.zs_encode(W)
+    n_bt = (N // 64) * (K // 64)
+    assert d.n_fallback == round(N * K * share) and 2 * d.n_fallback / n_bt > 256
+    assert (18 * d.n_fallback <= N * K and d.max_l_units * 16 * n_bt <= 3 * d.n_fallback) == loop
+    assert np.array_equal(gu.gpu_decompress(W), W)
+    for M in (5, 31, 40, 77, 150):              # every kernel that decodes
+        gu.check_gemm(W, inputs.activations(M, K, 56 + M))
+
+
 def test_gemm_specials(gu):
     """Finite specials: numeric check.  Inf/NaN: class check (NaN <-> NaN, Inf same sign)."""
     A = inputs.activations(16, 256, 9)
