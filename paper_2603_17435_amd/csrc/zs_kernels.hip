@@ -209,8 +209,9 @@ __device__ __forceinline__ StagedL stage_tile(const BlobView &bv, const TileRef 
 // and TensorCoreTile are stored row-major, in whole cache lines.  Bound by memory: 28672 x 4096 reads
 // and writes 399 MB in 77.7 us, 5.1 TB/s, the rate of a device copy (5.2); with half lines it
 // was 98.8 us.  4096 x 14336: 37.7 -> 33.9 us.  Without the non-temporal hint 83 and 44 us.
+// LINES = false stores each TensorCoreTile as it is decoded, in half lines (zs_decompress says when).
 // --------------------------------------------------------------------------------------
-template <int LW, int DEPTH, int WAVES, bool BASE_M1, Fallbacks CAREFUL>
+template <int LW, int DEPTH, int WAVES, bool BASE_M1, Fallbacks CAREFUL, bool LINES>
 __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uint16_t *out, int64_t ldw)
 {
     using S = Slot<LW>;
@@ -223,9 +224,10 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
     const uint32_t ring = tab + kTableBytes + wave * (DEPTH * S::kBytes);
     const uint32_t n_bt = (uint32_t)bv.strips * (uint32_t)bv.k_blocks;
     const uint32_t first = blockIdx.x * WAVES + wave, stride = gridDim.x * WAVES;
-    // what the lane stores, see below: row lane % 8 of eight, 16 bytes of its 128
+    // what the lane stores, see below: row lane % 8 of eight, 16 bytes of its 128; without LINES the row it
+    // decodes (FragTiles run N-fastest), 16 bytes of its 64
     const bool upper = (lane & 8u) != 0;
-    const uint32_t row = lane & 7u, col = (lane >> 4) * 8u + (lane & 8u) * 4u;
+    const uint32_t row = LINES ? lane & 7u : lane & 15u, col = (lane >> 4) * 8u + (LINES ? (lane & 8u) * 4u : 0u);
 
 #pragma unroll
     for (int j = 0; j < DEPTH - 1; ++j) {
@@ -259,6 +261,11 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
         u32x4 left[4]; // the TensorCoreTiles of the first k half, until their neighbours are decoded
         decode_block_tile<BASE_M1, 0, 0, CAREFUL>(tab, pa, h0, h_base, l_lane_of(slot + S::kH, slot + S::kL, lane), fs,
                                          [&](int tt, const u32x4 &w) {
+                                             if (!LINES) {
+                                                 __builtin_nontemporal_store(
+                                                     w, reinterpret_cast<u32x4 *>(dst + (int64_t)((tt & 3) * 16) * ldw + (tt >> 2) * 32));
+                                                 return;
+                                             }
                                              if (tt < 4) {
                                                  left[tt] = w;
                                                  return;
@@ -1348,7 +1355,7 @@ extern "C" int zs_decompress(const zs_desc *d, const void *blob_dev, uint16_t *W
     DeviceInfo di;
     if ((rc = device_info(&di)) != ZS_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    static std::atomic<uint64_t> lds_allowed[5];
+    static std::atomic<uint64_t> lds_allowed[8];
     auto launch = [&](auto kern, uint32_t lds, int waves, int site) {
         int r = allow_big_lds(kern, lds, di.id, lds_allowed[site]);
         if (r != ZS_OK) return r;
@@ -1357,19 +1364,29 @@ extern "C" int zs_decompress(const zs_desc *d, const void *blob_dev, uint16_t *W
         hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * waves), lds, s, bv, W_out_dev, ldw);
         return hipGetLastError() == hipSuccess ? (int)ZS_OK : (int)ZS_ERR_HIP;
     };
+    // Whole cache lines hold back the first half of a BlockTile's stores, which a wave with one or two
+    // BlockTiles does not catch up with, and the later the more it decodes.  Half / whole lines, 2 % fallbacks:
+    // 1024 x 1024 6.14 / 6.47 us, 3072 x 4096 9.92 / 10.5, 3840 x 4096 (15 BlockTiles per CU) 10.8 / 11.3, 4096 x 4096 11.8 /
+    // 11.5, 6144 x 4096 17.8 / 15.8; 4.4 %: 4096 x 4096 11.9 / 12.5, 4608 x 4096 (18) 15.1 / 15.9, 5120 x 4096 15.9 / 16.1, 6144 x
+    // 4096 18.0 / 16.8; 32 %: 4096 x 4096 15.9 / 16.3, 4608 x 4096 16.0 / 16.1, 5120 x 4096 17.0 / 16.7.
+    const bool lines = n_bt > (int64_t)(32 * d->n_fallback <= (uint64_t)n_bt * ZS_BT_ELEMS ? 15 : 18) * di.cus;
     const bool m1 = d->base_exp < 0;
     if (pick_l_window(d) == 512) {
         // eight waves with three tiles in flight each (measured against 7 x 3 with a 1 KB window,
         // 11 x 2, 10 x 2, 6 x 4 and 5 x 4: 2 to 10 % faster on the 8B shapes)
         constexpr uint32_t lds = kTableBytes + 8 * 3 * Slot<512>::kBytes;
         static_assert(lds <= kMaxLds, "variant does not fit the 160 KB of LDS");
-        return m1 ? launch(decompress_kernel<512, 3, 8, true, kLoop>, lds, 8, 0)
-                  : launch(decompress_kernel<512, 3, 8, false, kLoop>, lds, 8, 1);
+        return m1      ? launch(decompress_kernel<512, 3, 8, true, kLoop, true>, lds, 8, 0)
+               : lines ? launch(decompress_kernel<512, 3, 8, false, kLoop, true>, lds, 8, 1)
+                       : launch(decompress_kernel<512, 3, 8, false, kLoop, false>, lds, 8, 2);
     }
     constexpr uint32_t lds = kTableBytes + 7 * 2 * Slot<4096>::kBytes;
-    return m1                ? launch(decompress_kernel<4096, 2, 7, true, kMany>, lds, 7, 2)
-           : careful_loop(d) ? launch(decompress_kernel<4096, 2, 7, false, kLoop>, lds, 7, 3)
-                             : launch(decompress_kernel<4096, 2, 7, false, kMany>, lds, 7, 4);
+    if (m1) return launch(decompress_kernel<4096, 2, 7, true, kMany, true>, lds, 7, 3);
+    if (careful_loop(d))
+        return lines ? launch(decompress_kernel<4096, 2, 7, false, kLoop, true>, lds, 7, 4)
+                     : launch(decompress_kernel<4096, 2, 7, false, kLoop, false>, lds, 7, 5);
+    return lines ? launch(decompress_kernel<4096, 2, 7, false, kMany, true>, lds, 7, 6)
+                 : launch(decompress_kernel<4096, 2, 7, false, kMany, false>, lds, 7, 7);
 }
 
 extern "C" int zs_compute_units(void) { return cus_or_default(); }

@@ -39,6 +39,25 @@ def test_decompress_rows_and_padding(gu, pad):
     assert np.array_equal(got[:, :K], W) and (got[:, K:] == 0x5A5A).all()
 
 
+@pytest.mark.parametrize("N,K,pad", [(3840, 4096, 0), (3904, 4096, 8), (4608, 4096, 0), (4672, 4096, 24)])
+@pytest.mark.parametrize("kind", ["gauss", "rowscale", "spread"])
+def test_decompress_half_and_whole_lines(gu, kind, N, K, pad):
+    """Sizes on both sides of the change from stores of half cache lines to whole ones (15 BlockTiles for
+    every compute unit, 18 with many fallbacks), with each of the three decoders."""
+    import torch
+    rng = np.random.default_rng(57)
+    if kind == "spread":                        # 5 % of the weights outside the window, evenly
+        W = (rng.integers(0, 1 << 16, (N, K)) & 0x807F | 0x3F80).astype(np.uint16)
+        W[rng.random((N, K)) < 0.05] &= 0x9FFF
+    else:
+        W = inputs.make_weights(kind, N, K, seed=58)
+    blob, d = binding.zs_encode(W)
+    out = torch.full((N, K + pad), 0x5A5A, dtype=torch.int16, device="cuda")
+    binding.zs_decompress(d, gu.upload_blob(blob), out, ldw=K + pad)
+    got = out.cpu().numpy().view(np.uint16)
+    assert np.array_equal(got[:, :K], W) and (got[:, K:] == 0x5A5A).all()
+
+
 def test_decompress_all_bit_patterns(gu):
     W = np.random.default_rng(0).permutation(np.arange(65536, dtype=np.uint16)).reshape(256, 256)
     assert np.array_equal(gu.gpu_decompress(W), W)
