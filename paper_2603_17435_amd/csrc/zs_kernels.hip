@@ -917,8 +917,11 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         u32x4 frag[F][MT];
         const uint32_t strip0 = g0 / k_blocks;
         uint32_t strip = strip0, kb = g0 - strip0 * k_blocks; // of the tile being consumed
-        // k block of the half whose fragments are requested next.  (It wraps around with the strips, so
-        // the F halves asked for beyond the range's end are valid addresses too.)
+        // k block of the half whose fragments are requested next.  At the start nothing is asked for beyond
+        // the range's end: a range of one or two tiles would wait behind it (always F halves / what there is:
+        // 64 x 64, 256 tokens 7.9 / 6.5 us; 1024 x 1024, 128 tokens 14.9 / 14.1).  In the loop eight consumers keep to
+        // that; four ask on (valid addresses: it wraps around with the strips), since the branch costs them more
+        // than the loads (28672 x 4096, 96 tokens, with / without it 67.3 / 66.4 us; eight, 256 tokens, 126.8 / 127.5).
         uint32_t req_kb = kb;
         auto request = [&](int f, int kh) {
 #pragma unroll
@@ -934,7 +937,8 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         };
         clear_acc();
 #pragma unroll
-        for (int f = 0; f < F; ++f) request(f, f & 1);
+        for (int f = 0; f < F; ++f)
+            if (f < 2 || (uint32_t)(f / 2) < n_tiles) request(f, f & 1);
 
         uint32_t slot = 0, i = 0, in_strip = 0; // tile being consumed, tiles of its strip consumed so far
         // Decoded weights: each operand of the next tile is read as soon as the MFMAs of this tile's are issued.
@@ -971,8 +975,10 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
             if (lane == 0)
                 __hip_atomic_fetch_add((LdsU32)(ctl + kPcConsumed + 4 * slot), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             seen = poll_ready(slot_next + 1 == (uint32_t)R ? 0u : slot_next + 1);
-            request(f0, 0); // the halves F further on; both at once: they share the cache lines
-            request(f1, 1);
+            if (Q <= 4 || i + F / 2 < n_tiles) { // (see req_kb)
+                request(f0, 0); // the halves F further on; both at once: they share the cache lines
+                request(f1, 1);
+            }
             ++in_strip;
             const bool last_of_strip = kb + 1 == k_blocks;
             if (last_of_strip || i + 1 == n_tiles) {
