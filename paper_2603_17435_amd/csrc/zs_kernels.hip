@@ -634,25 +634,28 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
                 };
                 constexpr uint32_t kRows = kUnits / 64;
                 // A last contributor's round trips, one after the other, are what a small layer's call ends
-                // with.  Beyond four contributors to a strip as many partial tiles are read at a time as the
-                // registers hold, and only the tokens there are go through scratch memory (with up to four of
-                // the sixteen a quarter of a slot).  1024 x 4096, 16 contributors, whole slots three at a
-                // time / as here: 14.6 / 10.2 us at 1 token, 14.8 / 11.5 at 7, 14.7 / 13.5 at 16.  With four or fewer one
-                // batch of three is enough and its addresses are sooner formed (4096 x 4096, 1 token: 13.5 us, with
-                // batches of sixteen 13.9).  Three is also the batch at 32 tokens with up to seven streaming
-                // waves (beyond, a wave has 168 registers).
-                bool finished;
-                if (MT == 1 && b_hi - b_lo > 3) {
-                    if (M <= 4)
-                        finished = exchange(std::integral_constant<uint32_t, 1>{}, std::integral_constant<int, 16>{});
-                    else if (M <= 8)
-                        finished = exchange(std::integral_constant<uint32_t, 2>{}, std::integral_constant<int, 8>{});
-                    else
-                        finished = exchange(std::integral_constant<uint32_t, 4>{}, std::integral_constant<int, MT == 1 ? 5 : 1>{});
-                } else {
-                    finished = exchange(std::integral_constant<uint32_t, kRows>{},
-                                        std::integral_constant<int, (MT == 4 || (MT == 2 && WAVES > 7) ? 1 : 3)>{});
+                // with.  At up to 16 tokens and beyond four contributors to a strip as many partial tiles are read at
+                // a time as the registers hold, and only the tokens there are go through scratch memory (with up to
+                // four of the sixteen a quarter of a slot).  1024 x 4096, 16 contributors, whole slots three at a
+                // time / as here: 14.7 / 10.2 us at 1 token, 14.8 / 11.6 at 8, 14.8 / 13.9 at 16.  Where three at a time take
+                // no more round trips their addresses are sooner formed: up to four contributors (4096 x 4096,
+                // 1 token: 13.5 us, with batches of sixteen 13.9), and seven with whole slots (six others; 320 x 448, 16
+                // tokens, 9.6, with batches of five 9.9).  Three is also the batch at 32 tokens with up to seven
+                // streaming waves (beyond, a wave has 168 registers).
+                constexpr int kBatch = MT == 4 || (MT == 2 && WAVES > 7) ? 1 : 3;
+                bool finished = false, batched = false;
+                if constexpr (MT == 1) {
+                    batched = b_hi - b_lo > 3 && (M <= 8 || b_hi - b_lo != 6);
+                    if (batched) {
+                        if (M <= 4)
+                            finished = exchange(std::integral_constant<uint32_t, 1>{}, std::integral_constant<int, 16>{});
+                        else if (M <= 8)
+                            finished = exchange(std::integral_constant<uint32_t, 2>{}, std::integral_constant<int, 8>{});
+                        else
+                            finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, 5>{});
+                    }
                 }
+                if (!batched) finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, kBatch>{});
                 if (!finished) continue;
             }
             const uint32_t lane_c = opaque_lane();

@@ -180,10 +180,11 @@ def test_gemm_workgroup_counts(gu):
 
 
 @pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16])
-@pytest.mark.parametrize("contributors", [2, 6, 9, 10, 17, 18, 40])
+@pytest.mark.parametrize("contributors", [2, 4, 5, 6, 7, 8, 9, 10, 17, 18, 40])
 def test_gemm_exchange_batches(gu, contributors, M):
     """One strip summed from several workgroups, around the number of partial tiles that are read at a
-    time (5, 8 or 16 by the number of tokens); the scratch buffer is zero again afterwards."""
+    time (3, or 5, 8 and 16 by the number of tokens); the scratch
+    buffer is zero again afterwards."""
     import torch
     K = 64 * contributors                       # one BlockTile, so one workgroup, per contributor
     W, A = inputs.gaussian_weights(64, K, 70), inputs.activations(M, K, 71 + M)
