@@ -11,7 +11,13 @@ compiler's own waits.  A wait written by hand (inside inline assembly) is taken 
 hand-issued load before it: its count is the kernel author's statement about the instructions
 in between (the streaming loop waits with vmcnt(loads of the next tile), and both staging paths
 issue exactly that many), which a path-insensitive pass over two complementary branches cannot
-re-derive.  What this test does establish is that the registers stay untouched up to that wait."""
+re-derive.  What this test does establish is that the registers stay untouched up to that wait.
+
+Matrix instructions written in inline assembly are invisible to it as well: the compiler adds no
+wait states around them.  They accumulate in place, so between the MFMAs of one accumulator nothing
+else may touch it, and nothing may read or write it until SETTLED wait states after the last one; an
+operand that a vector instruction writes needs OPERAND wait states before the MFMA.  Every path is
+followed for that too."""
 import collections
 import os
 import re
@@ -53,9 +59,12 @@ def kernels(asm: str):
         yield km.group(1), ins
 
 
-def hazards(ins):
+SETTLED = 16  # what the kernels wait for; a 16x16x32 BF16 MFMA (four passes) needs less
+OPERAND = 2
+
+
+def successor_function(ins):
     label_at = {t[:-1]: i for i, (t, _) in enumerate(ins) if t.endswith(":")}
-    n = len(ins)
 
     def successors(i):
         t = ins[i][0]
@@ -69,7 +78,60 @@ def hazards(ins):
         if mn.startswith("s_cbranch"):
             return [label_at[t.split()[1]], i + 1]
         return [i + 1]
+    return successors
 
+
+def operands(text):
+    parts = text.split(None, 1)
+    return parts[0], [o.strip() for o in parts[1].split(",")] if len(parts) > 1 else []
+
+
+def mfma_hazards(ins):
+    """Instructions that break the rules above, {index: (text, registers)}."""
+    n, successors = len(ins), successor_function(ins)
+    state_in = [None] * n  # (accumulator register -> wait states since its MFMA, vector-written register -> wait states since)
+    state_in[0] = ({}, {})
+    work = collections.deque([0])
+    found = {}
+    while work:
+        i = work.popleft()
+        acc, written = (dict(x) for x in state_in[i])
+        text, inline = ins[i]
+        if not text.endswith(":"):
+            mn, ops = operands(text)
+            regs = [registers(o.split()[0]) for o in ops if o]
+            if inline and mn.startswith("v_mfma"):
+                dst, a, b, c = regs
+                bad = (a | b) & acc.keys() | (a | b | c) & written.keys()
+                if dst != c:
+                    bad |= dst | c
+                elif dst & acc.keys() and any(acc.get(r, (0, None))[1] != min(dst) for r in dst):
+                    bad |= dst  # overlaps another accumulator
+            else:
+                bad = set().union(*regs) & acc.keys() if regs else set()
+            if bad:
+                found.setdefault(i, (text, sorted(bad)))
+            wait = int(ops[0], 0) + 1 if mn == "s_nop" else 1
+            acc = {r: (k + wait, base) for r, (k, base) in acc.items() if k + wait < SETTLED}
+            written = {r: k + wait for r, k in written.items() if k + wait < OPERAND}
+            if inline and mn.startswith("v_mfma"):
+                acc.update({r: (0, min(dst)) for r in dst})
+            elif mn.startswith("v_") and regs:
+                written.update({r: 0 for r in regs[0]})
+        for s in successors(i):
+            if s >= n:
+                continue
+            old = state_in[s]
+            new = (acc, written) if old is None else tuple(
+                {r: min(x[r], y[r]) if r in x and r in y else x.get(r, y.get(r)) for r in x.keys() | y.keys()} for x, y in zip((acc, written), old))
+            if old is None or new != old:
+                state_in[s] = new
+                work.append(s)
+    return found
+
+
+def hazards(ins):
+    n, successors = len(ins), successor_function(ins)
     state_in = [None] * n  # register -> fewest vector-memory instructions issued since its load, over all paths
     state_in[0] = {}
     work = collections.deque([0])
@@ -79,9 +141,7 @@ def hazards(ins):
         cur = dict(state_in[i])
         text, inline = ins[i]
         if not text.endswith(":"):
-            parts = text.split(None, 1)
-            mn = parts[0]
-            ops = [o.strip() for o in parts[1].split(",")] if len(parts) > 1 else []
+            mn, ops = operands(text)
             if mn == "s_waitcnt":
                 m = re.search(r"vmcnt\((\d+)\)", text)
                 if m:
@@ -140,3 +200,34 @@ def test_no_register_of_a_hand_issued_load_is_touched_before_its_wait(kernel_asm
         found = hazards(ins)
         assert not found, f"{name}: {list(found.values())[:4]}"
     assert seen_loads > 0  # the streaming kernels issue their activation fragments by hand
+
+
+def test_checker_sees_planted_mfma_hazards():
+    """The same for matrix instructions, on hand-made code."""
+    def mfma(acc, a="v[20:23]", b="v[24:27]", c=None):
+        return (f"v_mfma_f32_16x16x32_bf16 {acc}, {a}, {b}, {c or acc}", True)
+    nop, end = ("s_nop 15", True), ("s_endpgm", False)
+    copy = ("v_mov_b32_e32 v30, v2", False)
+    assert not mfma_hazards([mfma("v[0:3]"), mfma("v[4:7]"), mfma("v[0:3]"), nop, copy, end])
+    assert mfma_hazards([mfma("v[0:3]"), ("s_nop 3", True), copy, end])                     # read too early
+    assert mfma_hazards([mfma("v[0:3]"), ("v_mov_b32_e32 v2, 0", False), nop, end])         # written too early
+    assert mfma_hazards([mfma("v[0:3]"), ("ds_read_b128 v[0:3], v40", False), nop, end])
+    assert mfma_hazards([mfma("v[0:3]"), mfma("v[2:5]"), nop, end])                         # overlapping accumulators
+    assert mfma_hazards([mfma("v[0:3]"), mfma("v[4:7]", a="v[0:3]"), nop, end])             # an accumulator as operand
+    assert mfma_hazards([mfma("v[0:3]", c="v[4:7]"), nop, end])                             # not in place
+    write = ("v_mov_b32_e32 v21, v40", False)
+    assert mfma_hazards([write, mfma("v[0:3]"), nop, end])                                  # operand just written
+    assert not mfma_hazards([write, ("s_nop 1", True), mfma("v[0:3]"), nop, end])
+    # one path of two without the wait, and a copy at the end of a loop
+    assert mfma_hazards([mfma("v[0:3]"), ("s_cbranch_scc1 .LBB0_1", False), nop, (".LBB0_1:", False), copy, end])
+    assert mfma_hazards([(".LBB0_1:", False), mfma("v[0:3]"), ("v_mov_b32_e32 v3, v9", False), ("s_cbranch_scc1 .LBB0_1", False), end])
+
+
+def test_hand_written_mfmas_keep_their_accumulators(kernel_asm):
+    kernels_with = 0
+    for name, ins in kernels(kernel_asm):
+        if any(inline and t.startswith("v_mfma") for t, inline in ins):
+            kernels_with += 1
+            found = mfma_hazards(ins)
+            assert not found, f"{name}: {list(found.values())[:4]}"
+    assert kernels_with > 0  # the consumers of the shared-decode kernel
