@@ -469,14 +469,15 @@ def test_encode_device_scan_workgroups(strips, k_blocks):
 
 def tied_windows(N, K):
     """Exponents 100..115 in equal shares: every window inside covers the same, the smallest start
-    wins, and a prediction from a part of the weights has no reason to agree."""
+    wins, and a prediction from a part of the weights has no reason to agree.  (Every BlockTile holds the
+    same number of weights in any of them: the counts that a wrong prediction left are right by chance.)"""
     return (((np.arange(N * K, dtype=np.uint32) % 16 + 100) << 7) | (np.arange(N * K, dtype=np.uint32) // 16 % 128)).astype(np.uint16).reshape(N, K)
 
 
 @pytest.mark.parametrize("kind,N,K", [("tied", 128, 192), ("tied", 1024, 1088), ("gauss", 192, 64 * 2732), ("student_t", 64, 576)])
 def test_encode_device_prediction_and_scan_edges(kind, N, K):
-    """Windows the sample cannot predict (the counts are taken again), and numbers of BlockTiles at the
-    edges of the prefix sum (8196 = one round of 8192 and half a thread more, 9 = one thread and one)."""
+    """Tied windows, and numbers of BlockTiles that leave a part of a thread's four in the prefix sum: 8196
+    (two workgroups of 4096 and one thread of a third) and 9 (two threads and a quarter of one)."""
     import torch
     W = tied_windows(N, K) if kind == "tied" else inputs.make_weights(kind, N, K, seed=91)
     blob, d = binding.zs_encode(W)
@@ -489,3 +490,43 @@ def test_encode_device_prediction_and_scan_edges(kind, N, K):
     got = out.cpu().numpy()
     assert np.array_equal(got[:d.total_bytes], blob)
     assert (got[d.total_bytes:] == 0xA5).all()
+
+
+def sampled_units(N, K):
+    """The 16-byte units of a row-major N x K matrix that the GPU packer predicts the window from."""
+    h = np.arange(2048, dtype=np.uint64) * 0x9E3779B1 & 0xFFFFFFFF
+    return (h * np.uint64(N * K // 8) >> np.uint64(32)).astype(np.int64)
+
+
+def best_window(exponents):
+    hist = np.bincount(exponents.ravel(), minlength=256)
+    return int(np.argmax(np.convolve(hist, np.ones(7, dtype=np.int64), "valid")))   # the first maximum
+
+
+@pytest.mark.parametrize("strips,k_blocks,a_strips", [(4, 4, 3), (16, 17, 9), (92, 90, 50)])
+def test_encode_device_wrong_prediction(strips, k_blocks, a_strips):
+    """Most strips hold exponents 100..106, the others and every sampled unit 110..116, and a tenth of all
+    weights lie outside both: the predicted window is 110, the right one 100, and with the one's counts a
+    BlockTile's segments would have the other's sizes.  92 x 90 BlockTiles are more than the waves of
+    a pass over them (16 in each of two workgroups on 256 compute units)."""
+    import torch
+    N, K = 64 * strips, 64 * k_blocks
+    rng = np.random.default_rng(93)
+    base = np.full((N, K), 110, dtype=np.uint16)
+    base[:64 * a_strips] = 100
+    base.reshape(-1, 8)[sampled_units(N, K)] = 110
+    exponent = base + rng.integers(0, 7, (N, K), dtype=np.uint16)
+    exponent[rng.random((N, K)) < 0.1] = 200
+    W = (exponent << 7 | rng.integers(0, 2, (N, K), dtype=np.uint16) << 15 | rng.integers(0, 128, (N, K), dtype=np.uint16)).astype(np.uint16)
+    assert best_window(exponent.reshape(-1, 8)[sampled_units(N, K)]) == 110 and best_window(exponent) == 100
+    tiles = exponent.reshape(strips, 64, k_blocks, 64)
+    units = [-(-((tiles >= lo) & (tiles < lo + 7)).sum((1, 3)) // 16) for lo in (100, 110)]
+    assert (units[0] != units[1]).mean() > 0.9
+    blob, d = binding.zs_encode(W)
+    assert d.base_exp == 99
+    cap = binding.zs_encode_bound(N, K)
+    out = torch.full((cap,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = torch.full((binding.ZS_ENCODE_WORKSPACE_BYTES,), 0xFF, dtype=torch.uint8, device="cuda")
+    d_dev = binding.zs_encode_device(torch.from_numpy(W.view(np.int16)).cuda(), N, K, out, cap, ws)
+    assert desc_fields(d_dev) == desc_fields(d)
+    assert np.array_equal(out.cpu().numpy()[:d.total_bytes], blob)
