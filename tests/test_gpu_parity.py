@@ -153,6 +153,21 @@ def test_gemm_specials(gu):
     gu.check_gemm(W, A)
 
 
+@pytest.mark.parametrize("M", [70, 128, 150, 256, 300])
+def test_gemm_shared_decode_specials(gu, M):
+    """Infinities and NaN through the producer / consumer kernel: weights of all kinds, then an activation
+    row of each kind at the first, an inner and the last token (beyond 256 in the second launch); the
+    rows beside them stay as they are."""
+    A = inputs.activations(M, 256, 64)
+    gu.check_gemm(inputs.special_weights(256, 256, 65, finite_only=True), A)
+    gu.check_gemm(inputs.special_weights(256, 256, 66, finite_only=False), A)
+    A = A.copy()
+    A[0, 3], A[M // 2, 17], A[M - 1, 255] = 0x7F80, 0xFF80, 0x7FC0      # +Inf, -Inf, NaN
+    C = gu.check_gemm(inputs.gaussian_weights(256, 256, 67), A)
+    assert not np.isfinite(C[[0, M // 2, M - 1]]).any()
+    assert np.isfinite(np.delete(C, [0, M // 2, M - 1], axis=0)).all()
+
+
 def test_gemm_every_config_small(gu):
     W = inputs.gaussian_weights(256, 1024, 12)
     for cfg, name in binding.zs_gemm_configs().items():
@@ -427,6 +442,25 @@ def test_gemm_strided_operands(gu):
     out = c.cpu().numpy()
     gu.assert_gemm_matches(out[:, :128], C_ref, S)
     assert (out[:, 128:] == 7.0).all()
+
+
+@pytest.mark.parametrize("M", [66, 128, 200, 256, 300])
+@pytest.mark.parametrize("wgs", [0, 1, 3])
+def test_gemm_shared_decode_strided_operands(gu, wgs, M):
+    """Row strides wider than the rows for the producer / consumer kernel, whole strips (one workgroup)
+    and shared ones; what lies between the rows is neither used nor written."""
+    import torch
+    N, K, lda, ldc = 192, 320, 376, 212
+    W, A = inputs.gaussian_weights(N, K, 18), inputs.activations(M, K, 19 + M)
+    blob, d = binding.zs_encode(W)
+    a = torch.full((M, lda), 0x7FC0, dtype=torch.int16, device="cuda")    # NaN between the rows
+    a[:, :K] = torch.from_numpy(A.view(np.int16)).cuda()
+    c = torch.full((M, ldc), 7.0, dtype=torch.float32, device="cuda")
+    binding.zs_gemm(d, gu.upload_blob(blob), a, c, M, lda=lda, ldc=ldc, config=binding.zs_gemm_pick_config(d, M) + 256 * wgs)
+    C_ref, S = oracle.gemm(A, W)
+    out = c.cpu().numpy()
+    gu.assert_gemm_matches(out[:, :N], C_ref, S)
+    assert (out[:, N:] == 7.0).all()
 
 
 def test_error_paths(gu):
