@@ -171,3 +171,36 @@ def test_bf16_output_full_size(gu, layer):
         C_ref, S = oracle.gemm(A, W, rows=rows, threads=8)
         assert (np.abs(got - C_ref) <= 1e-3 * S + 1e-6 + 2.0 ** -8 * np.abs(C_ref)).all()
         assert not ws.cpu().numpy().any()
+
+
+def test_encode_device_several_scan_rounds():
+    """More BlockTiles (257 x 1024) than 64 workgroups take in one round of 4096: the prefix sum carries on
+    from round to round.  The offsets against cumulative sums of the padded segment sizes, the sizes of
+    the descriptor, and the whole matrix back."""
+    strips, k_blocks = 257, 1024
+    N, K = 64 * strips, 64 * k_blocks
+    gen = torch.Generator(device="cuda").manual_seed(95)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device="cuda")
+    nh = torch.empty((strips, k_blocks), dtype=torch.int64, device="cuda")
+    for s in range(strips):
+        rows = W[64 * s:64 * s + 64]
+        rows.copy_(torch.randn((64, K), generator=gen, device="cuda"))
+        rows *= 0.02 * 2.0 ** (s % 3)  # neighbouring strips have different sizes
+    cap = binding.zs_encode_bound(N, K)
+    blob = torch.empty(cap, dtype=torch.uint8, device="cuda")
+    ws = torch.full((binding.ZS_ENCODE_WORKSPACE_BYTES,), 0xFF, dtype=torch.uint8, device="cuda")
+    d = binding.zs_encode_device(W, N, K, blob, cap, ws)
+    assert binding.zs_desc_validate(d) == 0
+    bits = W.view(torch.int16)
+    for s in range(strips):
+        e = (bits[64 * s:64 * s + 64].int() >> 7 & 0xFF) - (d.base_exp + 1)
+        nh[s] = ((e >= 0) & (e < 7)).view(64, k_blocks, 64).sum((0, 2))
+    nh = nh.view(-1)
+    offsets = blob[d.off_offsets:d.off_offsets + 8 * (nh.numel() + 1)].view(torch.int32).view(-1, 2).long() & 0xFFFFFFFF
+    for col, units in enumerate(((nh + 15) // 16, (2 * (4096 - nh) + 15) // 16)):
+        assert offsets[0, col] == 0 and torch.equal(offsets[1:, col], units.cumsum(0))
+        assert (d.h_bytes, d.l_bytes)[col] == 16 * int(units.sum()) and (d.max_h_units, d.max_l_units)[col] == int(units.max())
+    assert d.n_high == int(nh.sum()) and d.n_fallback == N * K - d.n_high
+    out = torch.empty((N, K), dtype=torch.int16, device="cuda")
+    binding.zs_decompress(d, blob, out)
+    assert torch.equal(out, bits)
