@@ -105,10 +105,14 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Tokens from which the decoupled pipeline is used.  Its cost is one decompression (the blob
 // read and the BF16 matrix written, whatever M) plus the dense GEMM; the fused kernels pay their
-// decode once per 256 tokens.  Measured on MI355X on the LLaMA-3 8B layer shapes: on the large
-// layers (GateUp, Down) the fused kernels win up to 256 tokens and lose from 512 on; on the
-// small ones (QKV, O: under 40 BlockTiles per compute unit), where the fused kernels are
-// dominated by fixed costs, the switch pays from 128 tokens.
+// decode once per 256 tokens.  Measured on MI355X on the LLaMA-3 8B layer shapes, us fused /
+// decoupled: on the large layers the fused kernels win up to 256 tokens and lose beyond (28672 x 4096,
+// 256 tokens 131 / 159, 320 tokens 186 / 155; 4096 x 14336, 256 73 / 108, 320 113 / 114).
+// On the small ones (under 40 BlockTiles per compute unit) the switch at 128 tokens dates from fused
+// kernels that were up to twice as slow at 65..256 tokens; with the present ones it would pay from
+// 257 at 6144 x 4096 (128 29 / 41, 256 44 / 55), 256 at 4096 x 4096 (128 24 / 37, 224 33 / 34, 256 36 / 34) and
+// 224 at 1024 x 4096 (128 18 / 23, 224 24.0 / 22.6).  It has stayed: zs_linear_path answers it, and programs
+// size their workspace by that.
 int64_t decoupled_from(const zs_desc *d)
 {
     const int64_t tiles_per_cu = (d->N / 64) * (d->K / 64) / zs_compute_units();

@@ -120,8 +120,10 @@ __device__ __forceinline__ uint32_t bin_total(const uint8_t *bins, uint32_t bin)
 // the matrix, spread over it by a multiplicative sequence (no row or column stride is favoured).
 // The prediction is only that: the counts taken with it are used if the full histogram agrees.
 // Bound by the latency of scattered reads from one compute unit: 8192 units took 21.9 us, 2048 take
-// 7.7 us, and 16 K weights still place the window of the test laws (neighbouring windows of N(0, s)
-// weights differ by 1.7 % of coverage, sixteen standard deviations of the sample).
+// 7.7 us, and 16 K weights still place the window of most laws: the best two windows of N(0, 0.02) weights
+// differ by 1.8 % of coverage, some fifteen standard deviations of the sample.  How far they differ depends on where
+// the scale lies between powers of two (nothing to 2.6 %); near a tie the prediction may fail, and the call then
+// reads the matrix once more (28672 x 4096: 203 us instead of 163).
 constexpr uint32_t kSampleUnits = 2048;
 __global__ __launch_bounds__(1024) void sample_kernel(const uint16_t *W, int64_t N, int64_t K, int64_t ldw, unsigned long long *hist,
                                                       Totals *totals)
@@ -219,8 +221,7 @@ __global__ __launch_bounds__(64 * kHistWaves) void recount_kernel(const uint16_t
 // counts of all BlockTiles before them itself: reading them again (4 bytes a BlockTile, from L2) costs less
 // than passing sums from one workgroup to the next.  Bound by latency: one workgroup that took the BlockTiles in
 // turn needed 16 us for the 28672 of a 28672 x 4096 layer; with seven the whole call went from 178 to 171 us.
-// (Unit sums stay below 2^32: the host
-// refuses larger matrices.)
+// (Unit sums stay below 2^32: the host refuses larger matrices.)
 constexpr uint32_t kScanRound = 4096, kScanWgs = 64;
 __global__ __launch_bounds__(1024) void scan_kernel(const uint32_t *counts, uint32_t *offsets, uint32_t n_bt, uint32_t per_wg,
                                                     const unsigned long long *hist, Totals *totals)

@@ -1328,7 +1328,10 @@ int launch_pc(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int6
 
 int variant_for(const zs_desc *d, int64_t M, int cus)
 {
-    // up to 64 tokens every wave decodes and multiplies for itself; beyond, the decode is shared
+    // Up to 64 tokens every wave decodes and multiplies for itself; beyond, the decode is shared.  (With its
+    // present consumers the shared decode would already pay from 33 tokens, where C is FP32: p64 against
+    // m64 at 50 tokens 19.4 / 26.4 us on 6144 x 4096, 16.1 / 22.3 on 4096 x 4096, 56.6 / 58.1 on 28672 x 4096,
+    // 31.7 / 36.1 on 4096 x 14336.  The line dates from consumers that were slower by a third.)
     const int lw = pick_l_window(d);
     const int tokens = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
     const bool shared_decode = tokens > 64;
