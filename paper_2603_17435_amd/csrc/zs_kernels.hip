@@ -643,19 +643,19 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
                 // tokens, 9.6, with batches of five 9.9).  Three is also the batch at 32 tokens with up to seven
                 // streaming waves (beyond, a wave has 168 registers).
                 constexpr int kBatch = MT == 4 || (MT == 2 && WAVES > 7) ? 1 : 3;
-                bool finished = false, batched = false;
-                if constexpr (MT == 1) {
-                    batched = b_hi - b_lo > 3 && (M <= 8 || b_hi - b_lo != 6);
-                    if (batched) {
-                        if (M <= 4)
-                            finished = exchange(std::integral_constant<uint32_t, 1>{}, std::integral_constant<int, 16>{});
-                        else if (M <= 8)
-                            finished = exchange(std::integral_constant<uint32_t, 2>{}, std::integral_constant<int, 8>{});
-                        else
-                            finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, 5>{});
-                    }
+                bool finished;
+                if (MT == 1 && b_hi - b_lo > 3) { // (seven contributors inside: an outer condition costs all others 0.1 us)
+                    if (M <= 4)
+                        finished = exchange(std::integral_constant<uint32_t, 1>{}, std::integral_constant<int, 16>{});
+                    else if (M <= 8)
+                        finished = exchange(std::integral_constant<uint32_t, 2>{}, std::integral_constant<int, 8>{});
+                    else if (b_hi - b_lo == 6)
+                        finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, kBatch>{});
+                    else
+                        finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, MT == 1 ? 5 : kBatch>{});
+                } else {
+                    finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, kBatch>{});
                 }
-                if (!batched) finished = exchange(std::integral_constant<uint32_t, kRows>{}, std::integral_constant<int, kBatch>{});
                 if (!finished) continue;
             }
             const uint32_t lane_c = opaque_lane();
