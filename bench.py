@@ -532,7 +532,7 @@ def run_variants(args):
     os.makedirs(os.path.dirname(os.path.abspath(args.variants)), exist_ok=True)
     with open(args.variants, "w") as f:
         f.write("# TCA-TBE format variants on a GateUp-shaped matrix (28672 x 4096)\n\n")
-        f.write(f"Command (GPU box, repository root): `python3 bench.py --variants {args.variants}`  \n")
+        f.write(f"Command (repository root): `python3 bench.py --variants {args.variants}`  \n")
         f.write(f"Environment: {json.dumps(environment())}  \n")
         f.write("Weights: `gauss` = N(0, 0.02); `rowscale` = N(0, 0.02) with a scale per row, log-uniform over three decades. "
                 "r = share of elements inside the window(s); model = Section 4.2's AverageBits(n) = r (n + 8) + (1 - r)(n + 16) "

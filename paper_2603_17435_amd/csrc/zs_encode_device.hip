@@ -165,7 +165,7 @@ __device__ __forceinline__ uint32_t fallbacks_of(const u32x4 (&v)[ZS_TT_PER_BT],
     return __builtin_amdgcn_readlane(wave_inclusive_scan(f), 63);
 }
 
-// Bound by the read of the matrix (235 MB of the 28672 x 4096 layer in 57 us, 4.1 TB/s; with one copy of
+// Bound by the read of the matrix (235 MB of the 28672 x 4096 layer in 45.5 us, 5.2 TB/s; with one copy of
 // the bins, one BlockTile per workgroup and a separate counting pass it was 482 + 36 us).  A wave takes whole
 // BlockTiles, so their counts need no exchange between waves; two workgroups of 16 waves on a
 // compute unit keep 256 KB of loads in flight, and the global histogram gets one addition per

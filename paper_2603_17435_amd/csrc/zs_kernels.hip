@@ -207,8 +207,8 @@ __device__ __forceinline__ StagedL stage_tile(const BlobView &bv, const TileRef 
 // --------------------------------------------------------------------------------------
 // Standalone decompression: waves take BlockTiles round-robin; 16 bytes (8 weights) per lane
 // and TensorCoreTile are stored row-major, in whole cache lines.  Bound by memory: 28672 x 4096 reads
-// and writes 399 MB in 77.7 us, 5.1 TB/s, the rate of a device copy (5.2); with half lines it
-// was 98.8 us.  4096 x 14336: 37.7 -> 33.9 us.  Without the non-temporal hint 83 and 44 us.
+// and writes 403 MB in 77.4 us, 5.2 TB/s, the rate of a device copy; with half lines it wrote 265 MB
+// for 235 and took 98.8 us.  4096 x 14336: 37.7 -> 33.8 us.  Without the non-temporal hint 83 and 44 us.
 // LINES = false stores each TensorCoreTile as it is decoded, in half lines (zs_decompress says when).
 // --------------------------------------------------------------------------------------
 template <int LW, int DEPTH, int WAVES, bool BASE_M1, Fallbacks CAREFUL, bool LINES>
@@ -895,7 +895,7 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
         // chain of four LDS round trips per tile (poll, operands, fence, hand back) is longer than the
         // decode: operands are read a tile ahead, "ready" is polled a tile before it is looked at, a
         // slot is handed back without a fence, and the consumers' waves go first on their SIMD.
-        // 4096 x 14336, 128 / 200 tokens: 61.5 / 88.1 -> 43 / 61 us; 28672 x 4096, 128 / 256: 93.7 / 161 -> 75 / 127 us.
+        // 4096 x 14336, 128 / 200 tokens: 61.5 / 88.1 -> 42.6 / 60 us; 28672 x 4096, 128 / 256: 93.7 / 161 -> 75 / 126 us.
         __builtin_amdgcn_s_setprio(2);
         const uint32_t c = wave - P;
         if ((int)c >= q_active) return;
