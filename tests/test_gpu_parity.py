@@ -198,8 +198,7 @@ def test_gemm_workgroup_counts(gu):
 @pytest.mark.parametrize("contributors", [2, 4, 5, 6, 7, 8, 9, 10, 17, 18, 40])
 def test_gemm_exchange_batches(gu, contributors, M):
     """One strip summed from several workgroups, around the number of partial tiles that are read at a
-    time (3, or 5, 8 and 16 by the number of tokens); the scratch
-    buffer is zero again afterwards."""
+    time (4 and 16); the scratch buffer is zero again afterwards."""
     import torch
     K = 64 * contributors                       # one BlockTile, so one workgroup, per contributor
     W, A = inputs.gaussian_weights(64, K, 70), inputs.activations(M, K, 71 + M)
@@ -212,6 +211,33 @@ def test_gemm_exchange_batches(gu, contributors, M):
         binding.zs_gemm(d, dev, a, c, M, workspace_dev=ws, workspace_bytes=ws.numel())
         gu.assert_gemm_matches(c.cpu().numpy(), C_ref, S)
         assert not ws.any()
+
+
+@pytest.mark.parametrize("config", ["m16_l0_w8", "m16_l0_w11", "m32_l0_w7", "m32_l0_w10", "m64_l0_w7", "m16_l4_w7", "m32_l4_w6", "m64_l4_w5"])
+def test_gemm_tasks_of_a_workgroup(gu, config):
+    """Ranges of one, two and many strip parts, whole and shared, first ones through the writer wave and the last one
+    through all waves, with every number of rows of four tokens; with sums in tiles of their own and in tiles
+    under a lock.  Every call is repeated and leaves the scratch buffer at zero."""
+    import torch
+    names = {v: k for k, v in binding.zs_gemm_configs().items()}
+    law = "gauss" if "_l0_" in config else "rowscale"
+    W = inputs.gaussian_weights(448, 1344, 90) if law == "gauss" else inputs.make_weights(law, 448, 1344, seed=91)
+    W_dec = oracle.decode(oracle.encode(W))
+    blob, d = binding.zs_encode(W)
+    dev = gu.upload_blob(blob)                  # 7 strips x 21 BlockTiles
+    tokens = int(config[1:3])
+    for M in sorted({1, 4, 5, tokens // 2 + 1, tokens - 3, tokens}):
+        A = inputs.activations(M, 1344, 92 + M)
+        C_ref, S = oracle.gemm(A, W_dec)
+        a = torch.from_numpy(A.view(np.int16)).cuda()
+        for wgs in (1, 2, 5, 7, 10, 17, 30, 147):
+            number = names[config] + 256 * wgs
+            ws = torch.zeros(binding.zs_gemm_workspace(d, M, number), dtype=torch.uint8, device="cuda")
+            for _ in range(2):
+                c = torch.full((M, 448), float("nan"), dtype=torch.float32, device="cuda")
+                binding.zs_gemm(d, dev, a, c, M, workspace_dev=ws, workspace_bytes=ws.numel(), config=number)
+                gu.assert_gemm_matches(c.cpu().numpy(), C_ref, S)
+            assert not ws.any()
 
 
 @pytest.mark.parametrize("law", ["gauss", "rowscale"])

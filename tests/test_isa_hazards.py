@@ -17,7 +17,11 @@ Matrix instructions written in inline assembly are invisible to it as well: the 
 wait states around them.  They accumulate in place, so between the MFMAs of one accumulator nothing
 else may touch it, and nothing may read or write it until SETTLED wait states after the last one; an
 operand that a vector instruction writes needs OPERAND wait states before the MFMA.  Every path is
-followed for that too."""
+followed for that too.
+
+A store of more than eight bytes a lane reads its registers while the next instruction issues; a vector
+instruction that overwrites them has to stay one wait state away.  The compiler sees to that inside a basic
+block, but not where the store ends one."""
 import collections
 import os
 import re
@@ -167,6 +171,33 @@ def hazards(ins):
     return found
 
 
+WIDE_STORE = re.compile(r"(global|buffer|flat|scratch)_store_dwordx[34]")
+
+
+def wide_store_hazards(ins):
+    """Vector instructions that overwrite the data of a wide store right behind it, on any path."""
+    successors, found = successor_function(ins), {}
+    for i, (text, _) in enumerate(ins):
+        mn, ops = operands(text)
+        if not WIDE_STORE.match(mn):
+            continue
+        data = registers(ops[0].split()[0] if mn.startswith("buffer") else ops[1].split()[0])
+        todo, seen = list(successors(i)), set()
+        while todo:
+            k = todo.pop()
+            if k >= len(ins) or k in seen:
+                continue
+            seen.add(k)
+            nxt = ins[k][0]
+            if nxt.endswith(":"):  # a label takes no time
+                todo += successors(k)
+                continue
+            m, o = operands(nxt)
+            if m.startswith("v_") and o and registers(o[0].split()[0]) & data:
+                found[k] = (text, nxt)
+    return found
+
+
 @pytest.fixture(scope="module")
 def kernel_asm(tmp_path_factory):
     out = tmp_path_factory.mktemp("isa") / "zs_kernels.s"
@@ -231,3 +262,23 @@ def test_hand_written_mfmas_keep_their_accumulators(kernel_asm):
             found = mfma_hazards(ins)
             assert not found, f"{name}: {list(found.values())[:4]}"
     assert kernels_with > 0  # the consumers of the shared-decode kernel
+
+
+def test_checker_sees_an_overwritten_store():
+    store, end = ("buffer_store_dwordx4 v[0:3], v9, s[4:7], s2 offen", False), ("s_endpgm", False)
+    over = ("v_mov_b32_e32 v2, 0", False)
+    assert wide_store_hazards([store, over, end])
+    assert wide_store_hazards([store, (".LBB0_1:", False), over, end])
+    assert wide_store_hazards([("global_store_dwordx4 v[8:9], v[0:3], off", False), (".LBB0_1:", False), over, end])
+    assert not wide_store_hazards([store, ("s_nop 0", False), over, end])
+    assert not wide_store_hazards([store, ("v_mov_b32_e32 v4, 0", False), over, end])
+    assert not wide_store_hazards([("global_store_dwordx2 v[8:9], v[2:3], off", False), over, end])
+
+
+def test_no_wide_store_loses_its_data(kernel_asm):
+    stores = 0
+    for name, ins in kernels(kernel_asm):
+        stores += sum(1 for t, _ in ins if WIDE_STORE.match(t))
+        found = wide_store_hazards(ins)
+        assert not found, f"{name}: {list(found.values())[:4]}"
+    assert stores > 0
