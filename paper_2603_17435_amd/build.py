@@ -16,6 +16,8 @@ COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I
 # purpose; the optimizer's wave-reduction wrapper would cost ~15 instructions around each.
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+          # scalar kernel arguments in front (gemm_stream_kernel) arrive in registers with the launch
+          "-mllvm", "-amdgpu-kernarg-preload-count=14",
           "-Wno-unused-command-line-argument", "-Wno-int-to-pointer-cast",
           # the LDS-direct staging code names m0 as clobbered (it writes it); clang warns that m0
           # is a reserved register, which is exactly why the compiler must be told

@@ -92,37 +92,42 @@ __device__ __forceinline__ constexpr int exp_byte_elem(int byte) { return byte =
 __device__ inline void build_tables(uint8_t *tab, int32_t base_exp)
 {
     const uint32_t base = base_exp < 0 ? 0u : (uint32_t)base_exp;
-    for (uint32_t m = threadIdx.x; m < 256; m += blockDim.x) {
-        uint32_t sel[4], fsel[4];
-        for (int reg = 0; reg < 4; ++reg) {
-            uint32_t s = 0, f = 0;
-            for (int half = 0; half < 2; ++half) {
-                const int e = elem_of(reg, half);
-                // index of element e among the in-window elements of the row (Algorithm 2)
-                const uint32_t idx_h = __builtin_popcount(m & ((1u << e) - 1u));
-                const uint32_t idx_l = (uint32_t)e - idx_h; // ... among the fallbacks
-                const bool high = (m >> e) & 1u;
-                const uint32_t hb = high ? idx_h : 0x0Cu; // 0x0C selects the constant 0
-                s |= (hb | (hb << 8)) << (16 * half);
-                // bytes 0..3 = the decoded register, 4..7 = the first two fallback halfwords
-                uint32_t lo = 2 * half, hi = 2 * half + 1;
-                if (!high && idx_l < 2) {
-                    lo = 4 + 2 * idx_l;
-                    hi = 5 + 2 * idx_l;
+    // (the selectors by the first 256 threads, the exponents by the next: four waves would do both one after the other)
+    for (uint32_t i = threadIdx.x; i < 512; i += blockDim.x) {
+        const uint32_t m = i & 255u;
+        if (i < 256) {
+            uint32_t sel[4], fsel[4];
+            for (int reg = 0; reg < 4; ++reg) {
+                uint32_t s = 0, f = 0;
+                for (int half = 0; half < 2; ++half) {
+                    const int e = elem_of(reg, half);
+                    // index of element e among the in-window elements of the row (Algorithm 2)
+                    const uint32_t idx_h = __builtin_popcount(m & ((1u << e) - 1u));
+                    const uint32_t idx_l = (uint32_t)e - idx_h; // ... among the fallbacks
+                    const bool high = (m >> e) & 1u;
+                    const uint32_t hb = high ? idx_h : 0x0Cu; // 0x0C selects the constant 0
+                    s |= (hb | (hb << 8)) << (16 * half);
+                    // bytes 0..3 = the decoded register, 4..7 = the first two fallback halfwords
+                    uint32_t lo = 2 * half, hi = 2 * half + 1;
+                    if (!high && idx_l < 2) {
+                        lo = 4 + 2 * idx_l;
+                        hi = 5 + 2 * idx_l;
+                    }
+                    f |= (lo | (hi << 8)) << (16 * half);
                 }
-                f |= (lo | (hi << 8)) << (16 * half);
+                sel[reg] = s;
+                fsel[reg] = f;
             }
-            sel[reg] = s;
-            fsel[reg] = f;
+            *reinterpret_cast<u32x4 *>(tab + kSelOff + 16 * m) = u32x4{sel[0], sel[1], sel[2], sel[3]};
+            *reinterpret_cast<u32x4 *>(tab + kFselOff + 16 * m) = u32x4{fsel[0], fsel[1], fsel[2], fsel[3]};
+            continue;
         }
-        *reinterpret_cast<u32x4 *>(tab + kSelOff + 16 * m) = u32x4{sel[0], sel[1], sel[2], sel[3]};
-        *reinterpret_cast<u32x4 *>(tab + kFselOff + 16 * m) = u32x4{fsel[0], fsel[1], fsel[2], fsel[3]};
         for (uint32_t plane = 0; plane < 3; ++plane) {
             uint32_t lo = 0, hi = 0;
-            for (int i = 0; i < 4; ++i) {
-                const int e = exp_byte_elem(i);
-                lo |= ((((m >> e) & 1u) << plane) + (plane == 0 ? base : 0u)) << (8 * i);
-                hi |= ((((m >> (e + 4)) & 1u) << plane) + (plane == 0 ? base : 0u)) << (8 * i);
+            for (int b = 0; b < 4; ++b) {
+                const int e = exp_byte_elem(b);
+                lo |= ((((m >> e) & 1u) << plane) + (plane == 0 ? base : 0u)) << (8 * b);
+                hi |= ((((m >> (e + 4)) & 1u) << plane) + (plane == 0 ? base : 0u)) << (8 * b);
             }
             *reinterpret_cast<u32x2 *>(tab + kExpOff + plane * 2048 + 8 * m) = u32x2{lo, hi};
         }

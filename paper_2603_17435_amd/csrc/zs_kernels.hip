@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstddef>
 #include <cstring>
 #include <type_traits>
 
@@ -375,25 +376,79 @@ __device__ __forceinline__ uint32_t bf16_rne(float x)
 // one of the next basic block (a lost word in the parked rows showed it): this goes behind such stores there.
 __device__ __forceinline__ void wide_store_done() { asm volatile("s_nop 0" ::: "memory"); }
 
+// Division of a number below 2^31 by d >= 1 with one multiplication: with 2^(l-1) < d <= 2^l and
+// magic = ceil(2^(31+l) / d) (below 2^32) the quotient is floor(n magic / 2^(31+l)), because magic d exceeds
+// 2^(31+l) by less than d <= 2^l.  A division by a run-time value is some thirty dependent vector
+// instructions; the kernels do it before their first load and between their last BlockTile and the end.
+struct Divider {
+    uint32_t d, magic;
+    static constexpr __host__ __device__ uint32_t log2_up(uint32_t d) { return d > 1 ? 32u - (uint32_t)__builtin_clz(d - 1) : 0u; }
+    static constexpr Divider by(uint32_t d) { return Divider{d, (uint32_t)(((1ull << (31 + log2_up(d))) + d - 1) / d)}; }
+    constexpr __host__ __device__ uint32_t operator()(uint32_t n) const
+    {
+        return (uint32_t)((uint64_t)(2 * n) * magic >> 32) >> log2_up(d);
+    }
+};
+constexpr bool divides(uint32_t d) // at both ends of the range and around the multiples of d there
+{
+    constexpr uint32_t top = (1u << 31) - 1;
+    const uint32_t last = top / d * d, at[] = {0u, d - 1, d, last - 1, last, top, top - 1};
+    for (uint32_t n : at)
+        if (n <= top && Divider::by(d)(n) != n / d) return false;
+    return true;
+}
+static_assert(divides(1) && divides(2) && divides(3) && divides(7) && divides(16) && divides(63) && divides(64) && divides(65) &&
+                  divides(224) && divides(448) && divides(65535) && divides(65537) && divides((1u << 30) - 1) &&
+                  divides((1u << 30) + 1) && divides((1u << 31) - 1), "division by multiplication");
+
 // The BlockTile sequence [0, total) is cut into `parts` contiguous ranges of q or q + 1
 // BlockTiles (the first r ranges have q + 1), total = parts * q + r.  The host fills the
 // struct, so that no kernel divides by a run-time value on its main path.
 struct RangeSplit {
     uint32_t total, parts, q, r;
+    uint32_t magic_q, magic_q1; // of the Dividers by q and q + 1
     __host__ __device__ uint32_t begin(uint32_t b) const { return b * q + (b < r ? b : r); }
     // the range that BlockTile g lies in
     __host__ __device__ uint32_t of(uint32_t g) const
     {
         const uint32_t wide = r * (q + 1);
-        return g < wide ? g / (q + 1) : r + (g - wide) / q;
+        return g < wide ? Divider{q + 1, magic_q1}(g) : r + Divider{q, magic_q}(g - wide);
     }
 };
 
+// Arguments of gemm_stream_kernel beyond the scalar ones in front.
+struct StreamArgs {
+    const uint16_t *A;
+    int64_t lda;
+    float *C;
+    int64_t ldc;
+    SharedSums ws;
+    int M;
+    int32_t base_exp;
+    uint32_t h_units, l_units, h_fast, l_fast, magic_q, magic_q1;
+};
+
+// The arguments in memory as the launch lays them out.
+struct StreamKernarg {
+    const void *offsets, *bitmaps, *H, *L;
+    uint32_t q, r, parts, k_blocks, magic_k;
+    StreamArgs args;
+};
+
+// The scalar arguments in front, 13 words, arrive in registers with the launch (the build asks for kernel
+// argument preloading): what the offsets of the first BlockTile depend on is there at the first instruction, and
+// the others are loaded behind those offsets, so that they are no link of the chain arguments -> offsets -> BlockTile.
+// The first BlockTile's loads are issued 430 to 1580 cycles earlier (the same stamped copies before and after); with the
+// divisions and the tables' halves on different waves, us: 1024 x 4096, one token 8.4 -> 8.2; 6144 x 4096, 7 tokens 14.55 -> 14.2;
+// 28672 x 4096, 16 tokens 38.6 -> 38.0, 50 tokens 52.9 -> 52.1; 4096 x 14336, 16 tokens, row-scaled 31.75 -> 31.1.
 template <int MT, int LW, int WAVES, bool BASE_M1, Fallbacks CAREFUL>
-__global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView bv, const uint16_t *A, int64_t lda,
-                                                                  float *C, int64_t ldc, int M, SharedSums ws,
-                                                                  RangeSplit rs)
+__global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32x2 *offsets, const uint8_t *bitmaps,
+                                                                  const uint8_t *H, const uint8_t *L, uint32_t q,
+                                                                  uint32_t r, uint32_t parts, uint32_t k_blocks,
+                                                                  uint32_t magic_k, StreamArgs)
 {
+    BlobView bv = {bitmaps, offsets, H, L, 0u, 0u, 0u, 0u, 0, (int32_t)k_blocks, 0}; // (the rest below)
+    const Divider by_k = {k_blocks, magic_k};
     using S = Slot<LW>;
     using Lds = StreamLds<MT, LW, WAVES>;
     constexpr int DEPTH = Lds::kDepth;
@@ -409,23 +464,14 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
     // the last byte any wave's ring can reach is Lds::kTotal, which is what the host requests
     const uint32_t rings = tab + Lds::kRings, ring = rings + wave * Lds::kRingBytes;
     const uint32_t m_lane = lane & 15u, kgrp = lane >> 4;
-    // B operand of the 16x16x32 MFMA: lane l holds token l % 16 and the 8 consecutive k that
-    // start at 8 * (l / 16).  Tokens >= M read token 0 instead (their columns are never stored).
-    uint32_t rowoff[MT];
-#pragma unroll
-    for (int j = 0; j < MT; ++j) {
-        const uint32_t m = j * 16 + m_lane;
-        rowoff[j] = ((int)m < M ? m : 0u) * (uint32_t)lda * 2u + kgrp * 16u;
-    }
-
     // this workgroup's range [g0, g1) of the BlockTile sequence and its tasks
-    const uint32_t k_blocks = (uint32_t)bv.k_blocks;
     // Workgroups are dealt out to the chip's eight dies round-robin (workgroup b runs on die
     // b % 8).  Neighbouring ranges share a strip and exchange partial tiles, so a die takes a
-    // run of consecutive ranges; a bijection on [0, gridDim.x) whenever 8 divides the grid.
-    const uint32_t range_id = (gridDim.x & 7u) == 0 ? (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    // run of consecutive ranges; a bijection on [0, parts) whenever 8 divides the grid.
+    const uint32_t range_id = (parts & 7u) == 0 ? (blockIdx.x & 7u) * (parts >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    RangeSplit rs = {0u, parts, q, r, 0u, 0u}; // (the total is not needed here, the magic numbers are loaded at the end)
     const uint32_t g0 = rs.begin(range_id), g1 = rs.begin(range_id + 1);
-    const uint32_t strip0 = g0 / k_blocks;
+    const uint32_t strip0 = by_k(g0);
     if (g0 >= g1) return;
     // Processing order: a range that touches several strips starts with its last one and then
     // runs from its beginning.  The (possibly shared) strips at both ends of the range are
@@ -433,7 +479,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
     // global memory, counting in, summing up) overlaps with the remaining work instead of
     // standing at the end of the kernel.  Tasks are numbered in processing order; the counter
     // that hands out BlockTiles counts positions c = 0 .. g1 - g0 - 1 in that order.
-    const uint32_t strip_last = (g1 - 1) / k_blocks, n_tasks = strip_last - strip0 + 1;
+    const uint32_t strip_last = by_k(g1 - 1), n_tasks = strip_last - strip0 + 1;
     const uint32_t rot = n_tasks > 1 ? g1 - strip_last * k_blocks : 0u; // BlockTiles taken before g0
     auto task_strip = [&](uint32_t j) { return rot ? (j ? strip0 + j - 1 : strip_last) : strip0 + j; };
 
@@ -484,8 +530,27 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
     if (wave < WAVES) {
         g_taken = wave;
         take_lookup();
-        stage(0);
     }
+    typedef const StreamArgs __attribute__((address_space(4))) *ConstArgs;
+    ConstArgs in_memory = (ConstArgs)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(StreamKernarg, args));
+    asm volatile("" : "+s"(in_memory)); // (not loaded before the offsets are asked for)
+    const uint16_t *const A = in_memory->A;
+    float *const C = in_memory->C;
+    const int64_t lda = in_memory->lda, ldc = in_memory->ldc;
+    const int M = in_memory->M;
+    const SharedSums ws = {in_memory->ws.count, in_memory->ws.tiles, in_memory->ws.mode, in_memory->ws.out_bf16, in_memory->ws.tiles_bytes};
+    bv.h_units = in_memory->h_units, bv.l_units = in_memory->l_units;
+    bv.h_fast = in_memory->h_fast, bv.l_fast = in_memory->l_fast, bv.base_exp = in_memory->base_exp;
+    if (wave < WAVES) stage(0);
+    // B operand of the 16x16x32 MFMA: lane l holds token l % 16 and the 8 consecutive k that
+    // start at 8 * (l / 16).  Tokens >= M read token 0 instead (their columns are never stored).
+    uint32_t rowoff[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        const uint32_t m = j * 16 + m_lane;
+        rowoff[j] = ((int)m < M ? m : 0u) * (uint32_t)lda * 2u + kgrp * 16u;
+    }
+
     build_tables(smem, bv.base_exp);
     constexpr uint32_t kClear = Lds::kOwnTiles ? 0 : 2 * kTileBytes; // (tiles of their own are written before they are read)
     for (uint32_t i = threadIdx.x; i < (kClear + kCtlBytes) / 4; i += blockDim.x)
@@ -499,6 +564,9 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
     // [first, last] contributing workgroup of a strip that this range holds only a part of
     auto contributors = [&](uint32_t strip, uint32_t &b_lo, uint32_t &b_hi) {
         if (task_tiles(strip) == k_blocks) return false;
+        ConstArgs again = in_memory;
+        asm volatile("" : "+s"(again)); // (not held in registers through the launch)
+        rs.magic_q = again->magic_q, rs.magic_q1 = again->magic_q1;
         b_lo = rs.of(strip * k_blocks), b_hi = rs.of((strip + 1) * k_blocks - 1);
         return true;
     };
@@ -636,10 +704,10 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(BlobView 
         constexpr uint32_t kAtATime = MT; // rows to a wave, so that one round serves up to 16 MT tokens with four waves
         const uint32_t strip = task_strip(n_tasks - 1), q0 = wave * kAtATime;
         if (q0 >= rows) return; // (one wave at least stays: wave 0)
+        uint32_t b_lo = 0, b_hi = 0; // (before the wait, which hides it)
+        const bool shared = contributors(strip, b_lo, b_hi), parked = shared && ws.mode == kSumParked;
         while (uniform(lds_poll(ctl + kCtlArrived)) != (uint32_t)WAVES) __builtin_amdgcn_s_sleep(1);
         asm volatile("" ::: "memory");
-        uint32_t b_lo = 0, b_hi = 0;
-        const bool shared = contributors(strip, b_lo, b_hi), parked = shared && ws.mode == kSumParked;
         const uint32_t l = opaque_lane();
 #pragma unroll
         for (uint32_t r = 0; r < kAtATime; ++r) {
@@ -963,7 +1031,7 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
 
     const uint32_t k_blocks = (uint32_t)bv.k_blocks;
     // neighbouring ranges (which share strips, and slabs of A) on one die, as in gemm_stream_kernel
-    const uint32_t range_id = (gridDim.x & 7u) == 0 ? (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const uint32_t range_id = (rs.parts & 7u) == 0 ? (blockIdx.x & 7u) * (rs.parts >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     const uint32_t g0 = rs.begin(range_id), g1 = rs.begin(range_id + 1);
 
     for (uint32_t i = threadIdx.x; i < kPcCtlBytes / 4; i += blockDim.x) *((LdsU32)(ctl + 4 * i)) = i == kPcNext / 4 ? g0 : 0u;
@@ -1276,7 +1344,11 @@ int cus_or_default()
     return device_info(&di) == ZS_OK ? di.cus : kDefaultCus;
 }
 
-RangeSplit split_ranges(uint32_t total, uint32_t parts) { return RangeSplit{total, parts, total / parts, total % parts}; }
+RangeSplit split_ranges(uint32_t total, uint32_t parts) // parts <= total
+{
+    const uint32_t q = total / parts;
+    return RangeSplit{total, parts, q, total % parts, Divider::by(q).magic, Divider::by(q + 1).magic};
+}
 
 // Window of the L segment staged in LDS, in bytes: twice the average BlockTile's segment
 // (BlockTiles with more take their fallbacks from global memory).
@@ -1382,7 +1454,9 @@ int launch_gemm(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, in
     } else {
         clear_shared_strips(bv, C, ldc, M, rs, s);
     }
-    hipLaunchKernelGGL(kern, dim3(wgs), dim3(64 * (WAVES + 1)), lds, s, bv, A, lda, C, ldc, M, ws, rs);
+    const StreamArgs args = {A, lda, C, ldc, ws, M, bv.base_exp, bv.h_units, bv.l_units, bv.h_fast, bv.l_fast, rs.magic_q, rs.magic_q1};
+    hipLaunchKernelGGL(kern, dim3(wgs), dim3(64 * (WAVES + 1)), lds, s, bv.offsets, bv.bitmaps, bv.H, bv.L, rs.q, rs.r, rs.parts,
+                       (uint32_t)bv.k_blocks, Divider::by((uint32_t)bv.k_blocks).magic, args);
     return hipGetLastError() == hipSuccess ? ZS_OK : ZS_ERR_HIP;
 }
 
