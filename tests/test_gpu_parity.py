@@ -420,6 +420,45 @@ def test_encode_device_equals_host_encoder(kind, N, K, pad):
         binding.zs_encode_device(w_dev, N, K, out, cap - 1, ws, ldw=K + pad)
 
 
+@pytest.mark.parametrize("n_threads", [3, 20])
+def test_encode_device_from_threads(n_threads):
+    """Calls under way at the same time, each on its own thread and stream, get their own totals: fewer than there
+    are slots of pinned memory for them, and more (those beyond copy)."""
+    import threading
+
+    import torch
+    shapes = [(64 * (1 + t % 5), 64 * (1 + t % 3)) for t in range(n_threads)]
+    kinds = ["gauss", "student_t", "rowscale"]
+    W = [inputs.make_weights(kinds[t % 3], *shapes[t], seed=200 + t) for t in range(n_threads)]
+    w_dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in W]
+    torch.cuda.synchronize()
+    got, start = [None] * n_threads, threading.Barrier(n_threads)
+
+    def work(t):
+        N, K = shapes[t]
+        cap, stream = binding.zs_encode_bound(N, K), torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            out = torch.empty(cap, dtype=torch.uint8, device="cuda")
+            ws = torch.empty(binding.ZS_ENCODE_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
+            start.wait()
+            results = []
+            for _ in range(8):
+                d = binding.zs_encode_device(w_dev[t], N, K, out, cap, ws, stream=stream.cuda_stream)
+                results.append((desc_fields(d), out[:d.total_bytes].cpu().numpy()))
+        got[t] = results
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(n_threads)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    for t in range(n_threads):
+        blob, d = binding.zs_encode(W[t])
+        assert got[t] is not None
+        for fields, b in got[t]:
+            assert fields == desc_fields(d) and np.array_equal(b, blob)
+
+
 @pytest.mark.parametrize("M", [1, 16, 31, 64, 150])
 def test_gemm_bf16_output(gu, M):
     """zs_gemm_bf16: the FP32 result rounded once to BF16.  Bound per element: the GEMM tolerance
