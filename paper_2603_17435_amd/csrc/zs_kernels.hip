@@ -310,10 +310,11 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
 // a shared counter (so a wave that shares its SIMD with fewer others simply takes more), each
 // staging its next tile with LDS-direct loads while it decodes and multiplies the current one.
 // A wave keeps the 64 x (16 MT) FP32 partial sums of one task in registers; when its next
-// tile belongs to another task it adds them, under a lock, into that task's accumulation
-// tile in LDS (two tiles, by parity of j) and reports how many BlockTiles they covered.  One
-// more wave, the writer, waits until a task's count is complete, takes the tile out of LDS,
-// hands the LDS tile back and stores it to C when the task is a whole strip.  The tile of a
+// tile belongs to another task it leaves them in an LDS tile of its own, or adds them, under a
+// lock, into that task's tile (two tiles, by parity of j) where LDS has no room, and reports how
+// many BlockTiles they covered.  One more wave, the writer, waits until a task's count is complete,
+// takes the sums out of LDS, hands the tile back and stores it to C when the task is a whole strip.
+// The last task is finished by the streaming waves themselves, a few rows each.  The tile of a
 // strip shared with other workgroups goes to global scratch instead, and the last workgroup
 // to contribute adds the tiles up and stores the strip (without scratch memory: FP32 atomics
 // onto a C cleared beforehand).  Streaming waves never meet at a barrier.
@@ -1273,8 +1274,9 @@ __global__ __launch_bounds__(64 * (P + Q)) void gemm_pc_kernel(BlobView bv, cons
 // Clears the columns of C that belong to strips shared by several workgroups of the ZipGEMM
 // launch that follows (they are summed with atomics).  The host lists those strips (a range
 // boundary that is not a multiple of k_blocks cuts exactly one strip, so there are fewer than
-// the number of workgroups); the list travels in the kernel arguments.  One workgroup per
-// listed strip.
+// the number of workgroups); the list travels in the kernel arguments.  A thread stores 16 bytes, a
+// workgroup 16 tokens of a strip: with one workgroup to a strip a thread stored up to sixteen times, one behind
+// the other (1024 x 4096, 128 tokens 16.3 -> 15.7 us, 1024 x 1024 14.05 -> 13.55, 4096 x 14336, 200 tokens 60.7 -> 60.4).
 constexpr int kMaxSharedStrips = 512;
 struct SharedStrips {
     uint32_t n;
@@ -1283,11 +1285,8 @@ struct SharedStrips {
 
 __global__ void clear_shared_strips_kernel(float *C, int64_t ldc, int M, SharedStrips list)
 {
-    const uint32_t strip = list.strip[blockIdx.x];
-    for (uint32_t i = threadIdx.x; i < (uint32_t)M * 16u; i += blockDim.x) {
-        const uint32_t m = i >> 4, c = i & 15u;
-        *reinterpret_cast<f32x4 *>(C + (int64_t)m * ldc + (int64_t)strip * 64 + 4 * c) = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    const uint32_t strip = list.strip[blockIdx.x], m = blockIdx.y * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15u;
+    if (m < (uint32_t)M) *reinterpret_cast<f32x4 *>(C + (int64_t)m * ldc + (int64_t)strip * 64 + 4 * c) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // --------------------------------------------------------------------------------------
@@ -1424,11 +1423,11 @@ void clear_shared_strips(const BlobView &bv, float *C, int64_t ldc, int M, const
         if (list.n && list.strip[list.n - 1] == strip) continue; // boundaries ascend: duplicates are adjacent
         list.strip[list.n++] = strip;
         if (list.n == (uint32_t)kMaxSharedStrips) { // flush a full list
-            hipLaunchKernelGGL(clear_shared_strips_kernel, dim3(list.n), dim3(256), 0, s, C, ldc, M, list);
+            hipLaunchKernelGGL(clear_shared_strips_kernel, dim3(list.n, ((unsigned)M + 15) / 16), dim3(256), 0, s, C, ldc, M, list);
             list.n = 0;
         }
     }
-    if (list.n) hipLaunchKernelGGL(clear_shared_strips_kernel, dim3(list.n), dim3(256), 0, s, C, ldc, M, list);
+    if (list.n) hipLaunchKernelGGL(clear_shared_strips_kernel, dim3(list.n, ((unsigned)M + 15) / 16), dim3(256), 0, s, C, ldc, M, list);
 }
 
 // Layout of the scratch buffer of gemm_stream_kernel: kMaxSharedCounters counter words (zero
@@ -1497,10 +1496,9 @@ int launch_pc(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, int6
 
 int variant_for(const zs_desc *d, int64_t M, int cus)
 {
-    // Up to 64 tokens every wave decodes and multiplies for itself; beyond, the decode is shared.  (With its
-    // present consumers the shared decode would already pay from 33 tokens, where C is FP32: p64 against
-    // m64 at 50 tokens 19.4 / 26.4 us on 6144 x 4096, 16.1 / 22.3 on 4096 x 4096, 56.6 / 58.1 on 28672 x 4096,
-    // 31.7 / 36.1 on 4096 x 14336.  The line dates from consumers that were slower by a third.)
+    // Up to 64 tokens every wave decodes and multiplies for itself; beyond, the decode is shared.  (From 33
+    // tokens, FP32 output, p64 / m64: 50 tokens, 6144 x 4096 20.2 / 24.4 us, 1024 x 4096 11.8 / 16.7; but 4096 x 4096, 48 tokens, 16.1 / 15.5;
+    // 64 tokens, 8192 x 4096 23.7 / 21.5, 28672 x 4096 57.3 / 53.3, 4096 x 14336 33.2 / 30.7.)
     const int lw = pick_l_window(d);
     const int tokens = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
     const bool shared_decode = tokens > 64;
