@@ -373,11 +373,6 @@ __device__ __forceinline__ uint32_t bf16_rne(float x)
     return (u & 0x7FFFFFFFu) > 0x7F800000u ? ((u >> 16) | 0x40u) : rounded;
 }
 
-// A store of more than eight bytes a lane still reads its registers while the next instruction issues.  The
-// compiler keeps a vector instruction that overwrites them one wait state away, but not where that is the first
-// one of the next basic block (a lost word in the parked rows showed it): this goes behind such stores there.
-__device__ __forceinline__ void wide_store_done() { asm volatile("s_nop 0" ::: "memory"); }
-
 // Division of a number below 2^31 by d >= 1 with one multiplication: with 2^(l-1) < d <= 2^l and
 // magic = ceil(2^(31+l) / d) (below 2^32) the quotient is floor(n magic / 2^(31+l)), because magic d exceeds
 // 2^(31+l) by less than d <= 2^l.  A division by a run-time value is some thirty dependent vector
@@ -594,7 +589,6 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
                 u32x2{bf16_rne(v.x) | (bf16_rne(v.y) << 16), bf16_rne(v.z) | (bf16_rne(v.w) << 16)};
         else
             *reinterpret_cast<f32x4 *>(C + at) = v;
-        wide_store_done();
     };
     auto add_row = [&](uint32_t strip, uint32_t q, uint32_t l, const f32x4 &v) { // kSumCleared
         const uint32_t m = 4 * q + (l >> 4);
@@ -613,8 +607,13 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
     // the chip's dies without cache-wide write-backs or invalidations), and that the
     // hardware checks against the size of the area (an out-of-range read returns zero,
     // an out-of-range write is dropped).  "Volatile": the polling reads must be repeated.
+    // Stores have the whole offset in the lanes' registers (store_unit): a store of more than eight bytes a lane still
+    // reads its data while the next instructions issue, and the compiler keeps the two wait states before a
+    // vector instruction overwrites them, except behind a buffer store with a scalar register as offset, where it
+    // keeps none.  A word parked by such a store was seen lost; how many that form needs is not known, so it is not used.
     constexpr int kCoherent = 16 | (int)0x80000000u; // sc1 | volatile (compiler-level)
     const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(ws.tiles, 0, (int)ws.tiles_bytes, 0x00020000);
+    auto store_unit = [&](const u32x4 &w, uint32_t at) { __builtin_amdgcn_raw_buffer_store_b128(w, slots, at, 0, kCoherent); };
     // byte offset of the slot of workgroup b for this strip: slot 0 of a workgroup holds
     // the strip its range starts in, slot 1 the one it ends in
     auto slot_of = [&](uint32_t strip, uint32_t b) {
@@ -627,8 +626,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
         u32x4 w = __builtin_bit_cast(u32x4, v);
         w.x = w.x ? w.x : 0x80000000u, w.y = w.y ? w.y : 0x80000000u;
         w.z = w.z ? w.z : 0x80000000u, w.w = w.w ? w.w : 0x80000000u;
-        __builtin_amdgcn_raw_buffer_store_b128(w, slots, l * 16, slot_of(strip, range_id) + q * 1024, kCoherent);
-        wide_store_done();
+        store_unit(w, l * 16 + (slot_of(strip, range_id) + q * 1024));
     };
     // Partial rows in flight: ROWS rows from row q on, of CNT contributors from workgroup b on (the last one
     // again where there are fewer: a load that is made or not would be waited for by itself).
@@ -658,7 +656,8 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
             __builtin_amdgcn_s_sleep(1);
             request_rows(t, slot_lo, b_lo, q, l, b, b_hi);
         }
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
+        u32x4 zero4 = {0u, 0u, 0u, 0u};
+        asm volatile("" : "+v"(zero4)); // (formed here: held through the writer's loop it does not fit the registers)
 #pragma unroll
         for (uint32_t i = 0; i < CNT; ++i)
             if (b + i <= b_hi) {
@@ -667,8 +666,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
                 for (uint32_t r = 0; r < ROWS; ++r) {
                     sum[r] += __builtin_bit_cast(f32x4, t[r][i]);
                     // (same address as the load above, same wave: stays behind it)
-                    if (r == 0 || q + r < rows) __builtin_amdgcn_raw_buffer_store_b128(zero4, slots, l * 16, slot + r * 1024, kCoherent);
-                    wide_store_done();
+                    if (r == 0 || q + r < rows) store_unit(zero4, l * 16 + (slot + r * 1024));
                 }
             }
     };

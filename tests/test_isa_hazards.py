@@ -19,9 +19,10 @@ else may touch it, and nothing may read or write it until SETTLED wait states af
 operand that a vector instruction writes needs OPERAND wait states before the MFMA.  Every path is
 followed for that too.
 
-A store of more than eight bytes a lane reads its registers while the next instruction issues; a vector
-instruction that overwrites them has to stay one wait state away.  The compiler sees to that inside a basic
-block, but not where the store ends one."""
+A store of more than eight bytes a lane reads its registers while the next instructions issue; a vector
+instruction that overwrites them has to stay STORED wait states away.  The compiler keeps them, across the ends of
+basic blocks too, except behind a buffer store with its offset in a scalar register, where it keeps none.  Every path
+behind every such store of every kernel source is followed, and the scalar form is not used."""
 import collections
 import os
 import re
@@ -172,40 +173,54 @@ def hazards(ins):
 
 
 WIDE_STORE = re.compile(r"(global|buffer|flat|scratch)_store_dwordx[34]")
+STORED = 2
 
 
 def wide_store_hazards(ins):
-    """Vector instructions that overwrite the data of a wide store right behind it, on any path."""
+    """Vector instructions that overwrite the data of a wide store fewer than STORED wait states behind it, on any
+    path; and wide buffer stores with a scalar register as offset."""
     successors, found = successor_function(ins), {}
     for i, (text, _) in enumerate(ins):
         mn, ops = operands(text)
         if not WIDE_STORE.match(mn):
             continue
+        if mn.startswith("buffer") and re.match(r"(s\d+|m0)\b", ops[3]):
+            found[i] = (text, "scalar offset")
         data = registers(ops[0].split()[0] if mn.startswith("buffer") else ops[1].split()[0])
-        todo, seen = list(successors(i)), set()
+        assert data, text
+        todo, fewest = [(k, 0) for k in successors(i)], {}
         while todo:
-            k = todo.pop()
-            if k >= len(ins) or k in seen:
+            k, states = todo.pop()
+            if k >= len(ins) or states >= STORED or fewest.get(k, STORED) <= states:
                 continue
-            seen.add(k)
+            fewest[k] = states
             nxt = ins[k][0]
-            if nxt.endswith(":"):  # a label takes no time
-                todo += successors(k)
-                continue
-            m, o = operands(nxt)
-            if m.startswith("v_") and o and registers(o[0].split()[0]) & data:
-                found[k] = (text, nxt)
+            if not nxt.endswith(":"):  # (a label takes no time)
+                m, o = operands(nxt)
+                if m.startswith("v_") and o and registers(o[0].split()[0]) & data:
+                    found[k] = (text, nxt)
+                states += int(o[0], 0) + 1 if m == "s_nop" else 1
+            todo += [(s, states) for s in successors(k)]
     return found
 
 
 @pytest.fixture(scope="module")
-def kernel_asm(tmp_path_factory):
-    out = tmp_path_factory.mktemp("isa") / "zs_kernels.s"
-    src = os.path.join(zs_build.CSRC, "zs_kernels.hip")
-    cmd = [zs_build.HIPCC, "-S", "--cuda-device-only", src, "-o", str(out)] + \
-          [f for f in zs_build.COMMON if f != "-fPIC"] + zs_build.DEVICE
-    subprocess.run(cmd, check=True, capture_output=True)
-    return out.read_text()
+def asm_of(tmp_path_factory):
+    """The generated code of every kernel source, {file name: text}."""
+    out = tmp_path_factory.mktemp("isa")
+    texts = {}
+    for src in (s for s in zs_build.sources() if s.endswith(".hip")):
+        to = out / (os.path.basename(src) + ".s")
+        cmd = [zs_build.HIPCC, "-S", "--cuda-device-only", src, "-o", str(to)] + \
+              [f for f in zs_build.COMMON if f != "-fPIC"] + zs_build.DEVICE
+        subprocess.run(cmd, check=True, capture_output=True)
+        texts[os.path.basename(src)] = to.read_text()
+    return texts
+
+
+@pytest.fixture(scope="module")
+def kernel_asm(asm_of):
+    return asm_of["zs_kernels.hip"]
 
 
 def test_checker_sees_a_planted_hazard():
@@ -265,20 +280,34 @@ def test_hand_written_mfmas_keep_their_accumulators(kernel_asm):
 
 
 def test_checker_sees_an_overwritten_store():
-    store, end = ("buffer_store_dwordx4 v[0:3], v9, s[4:7], s2 offen", False), ("s_endpgm", False)
-    over = ("v_mov_b32_e32 v2, 0", False)
+    store, end = ("buffer_store_dwordx4 v[0:3], v9, s[4:7], 0 offen offset:16 sc1", False), ("s_endpgm", False)
+    over, label, other = ("v_mov_b32_e32 v2, 0", False), (".LBB0_1:", False), ("s_add_u32 s0, s0, s1", False)
+
+    def nop(n):
+        return (f"s_nop {n}", False)
     assert wide_store_hazards([store, over, end])
-    assert wide_store_hazards([store, (".LBB0_1:", False), over, end])
-    assert wide_store_hazards([("global_store_dwordx4 v[8:9], v[0:3], off", False), (".LBB0_1:", False), over, end])
-    assert not wide_store_hazards([store, ("s_nop 0", False), over, end])
-    assert not wide_store_hazards([store, ("v_mov_b32_e32 v4, 0", False), over, end])
+    assert wide_store_hazards([store, label, over, end])
+    assert wide_store_hazards([("global_store_dwordx4 v[8:9], v[0:3], off", False), label, over, end])
+    assert wide_store_hazards([store, nop(0), over, end])
+    assert wide_store_hazards([store, other, label, over, end])
+    assert not wide_store_hazards([store, nop(1), over, end])
+    assert not wide_store_hazards([store, nop(0), label, other, over, end])
+    assert not wide_store_hazards([store, ("v_mov_b32_e32 v4, 0", False), ("v_mov_b32_e32 v5, 0", False), over, end])
     assert not wide_store_hazards([("global_store_dwordx2 v[8:9], v[2:3], off", False), over, end])
+    # one path of two with the wait states, and a loop that comes back
+    branch = ("s_cbranch_scc1 .LBB0_1", False)
+    assert wide_store_hazards([store, branch, nop(0), label, over, end])
+    assert not wide_store_hazards([store, nop(0), branch, nop(3), label, over, end])
+    assert wide_store_hazards([label, over, store, branch, end])
+    # the offset in a scalar register
+    assert wide_store_hazards([("buffer_store_dwordx4 v[0:3], v9, s[4:7], s2 offen sc1", False), nop(3), end])
 
 
-def test_no_wide_store_loses_its_data(kernel_asm):
-    stores = 0
-    for name, ins in kernels(kernel_asm):
-        stores += sum(1 for t, _ in ins if WIDE_STORE.match(t))
-        found = wide_store_hazards(ins)
-        assert not found, f"{name}: {list(found.values())[:4]}"
-    assert stores > 0
+def test_no_wide_store_loses_its_data(asm_of):
+    stores = {}
+    for source, asm in asm_of.items():
+        for name, ins in kernels(asm):
+            stores[source] = stores.get(source, 0) + sum(1 for t, _ in ins if WIDE_STORE.match(t))
+            found = wide_store_hazards(ins)
+            assert not found, f"{source}: {name}: {list(found.values())[:4]}"
+    assert len(stores) == 3 and all(stores.values())
