@@ -511,6 +511,7 @@ extern "C" int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int
                        n_bt, hist_dev, totals_dev, counts_dev);
     hipLaunchKernelGGL(recount_kernel, at_most((n_bt + kHistWaves - 1) / kHistWaves, wgs), dim3(64 * kHistWaves), 0, s, W_dev, ldw, k_blocks,
                        n_bt, hist_dev, totals_dev, counts_dev);
+    if (!ok(hipGetLastError())) return ZS_ERR_HIP; // (the pinned slot clears errors of its own, and these with them)
     HostTotals pinned;
     Totals *const mapped = pinned.device();
     const uint32_t per_wg = kScanRound * ((n_bt + kScanRound * kScanWgs - 1) / (kScanRound * kScanWgs));
