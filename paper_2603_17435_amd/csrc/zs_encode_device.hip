@@ -324,29 +324,34 @@ public:
         });
         for (int i = 0; page_ && i < kSlots && slot_ < 0; ++i)
             if (!taken_[i].exchange(true, std::memory_order_acquire)) slot_ = i;
+        void *p = nullptr;
+        if (host() && hipHostGetDevicePointer(&p, host(), 0) != hipSuccess) {
+            (void)hipGetLastError(); // (the call copies)
+            give_back();
+            p = nullptr;
+        }
+        device_ = static_cast<Totals *>(p);
     }
-    ~HostTotals()
-    {
-        if (slot_ >= 0) taken_[slot_].store(false, std::memory_order_release);
-    }
+    ~HostTotals() { give_back(); }
     HostTotals(const HostTotals &) = delete;
     HostTotals &operator=(const HostTotals &) = delete;
     Totals *host() const { return slot_ < 0 ? nullptr : reinterpret_cast<Totals *>(page_ + slot_ * kSlotBytes); }
-    // the same for the current device
-    Totals *device() const
-    {
-        void *p = nullptr;
-        return host() && hipHostGetDevicePointer(&p, host(), 0) == hipSuccess ? static_cast<Totals *>(p) : nullptr;
-    }
-
-    void keep() { slot_ = -1; } // not given back: the GPU may still write it
+    Totals *device() const { return device_; } // the same for the device that was current
+    void keep() { slot_ = -1; }                // not given back: the GPU may still write it
 
 private:
+    void give_back()
+    {
+        if (slot_ >= 0) taken_[slot_].store(false, std::memory_order_release);
+        slot_ = -1;
+    }
+
     static constexpr int kSlots = 16, kSlotBytes = 64;
     static_assert(sizeof(Totals) <= kSlotBytes, "a slot holds the totals");
     static inline uint8_t *page_ = nullptr;
     static inline std::atomic<bool> taken_[kSlots] = {};
     int slot_ = -1;
+    Totals *device_ = nullptr;
 };
 
 // One wave per BlockTile.  A lane owns one FragTile row per TensorCoreTile: its byte of each

@@ -144,6 +144,11 @@ int main(int argc, char **argv)
     } else if (scenario == "no_pinned_memory") {
         malloc_fails = true;
         calls(3, ZS_OK, 3, "no pinned memory");
+    } else if (scenario == "no_mapping") { // and the slots are there again when it works
+        mapping_fails = true;
+        calls(20, ZS_OK, 20, "no device address");
+        mapping_fails = false;
+        calls(3, ZS_OK, 0, "afterwards");
     } else if (scenario == "threads") { // one more than there are slots, all under way at a time
         constexpr int kThreads = 17;
         wait_for = kThreads;

@@ -28,7 +28,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["plain", "no_pinned_memory", "threads", "failed_wait", "failed_launch",
+@pytest.mark.parametrize("scenario", ["plain", "no_pinned_memory", "no_mapping", "threads", "failed_wait", "failed_launch",
                                       "failed_launch no_pinned_memory"])
 def test_packer_host_code(program, scenario):
     done = subprocess.run([str(program)] + scenario.split(), capture_output=True, text=True, timeout=60)
