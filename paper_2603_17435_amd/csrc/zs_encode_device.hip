@@ -312,8 +312,15 @@ __global__ __launch_bounds__(1024) void scan_kernel(const uint32_t *counts, uint
 // copies instead.
 class HostTotals {
 public:
-    HostTotals()
+    explicit HostTotals(hipStream_t s)
     {
+        // Under capture the wait is refused, and a slot would be kept for good by each such call.
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+            (void)hipGetLastError(); // (the wait will say)
+            return;
+        }
+        if (capture != hipStreamCaptureStatusNone) return;
         static std::once_flag once;
         std::call_once(once, [] {
             void *p = nullptr;
@@ -517,7 +524,7 @@ extern "C" int zs_encode_device(const uint16_t *W_dev, int64_t N, int64_t K, int
     hipLaunchKernelGGL(recount_kernel, at_most((n_bt + kHistWaves - 1) / kHistWaves, wgs), dim3(64 * kHistWaves), 0, s, W_dev, ldw, k_blocks,
                        n_bt, hist_dev, totals_dev, counts_dev);
     if (!ok(hipGetLastError())) return ZS_ERR_HIP; // (the pinned slot clears errors of its own, and these with them)
-    HostTotals pinned;
+    HostTotals pinned(s);
     Totals *const mapped = pinned.device();
     const uint32_t per_wg = kScanRound * ((n_bt + kScanRound * kScanWgs - 1) / (kScanRound * kScanWgs));
     hipLaunchKernelGGL(scan_kernel, dim3((n_bt + per_wg - 1) / per_wg), dim3(1024), 0, s, counts_dev, offsets_dev, n_bt, per_wg, hist_dev,

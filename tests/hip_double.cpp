@@ -1,6 +1,6 @@
 // A stand-in for the HIP runtime, linked with the host half of zs_encode_device.hip on a machine without a GPU: what
-// the packer's host code does when a runtime call fails and when more calls are under way than there are slots of
-// pinned memory.  No kernel runs; the launch of scan_kernel leaves a fixed set
+// the packer's host code does when a runtime call fails, when the stream is being captured, and when more calls are
+// under way than there are slots of pinned memory.  No kernel runs; the launch of scan_kernel leaves a fixed set
 // of totals where the kernel would, and the copy of the totals delivers the same ones.
 // The scenario is the program's argument; the exit status is 0 when everything in it held.
 #include <hip/hip_runtime_api.h>
@@ -36,7 +36,7 @@ std::map<const void *, std::string> &names() // of the kernels, by their host ad
 thread_local hipError_t last = hipSuccess;
 std::atomic<int> copies{0};
 std::set<void *> slots_seen; // pinned slots that a launch of scan_kernel was given
-std::atomic<bool> malloc_fails{false}, mapping_fails{false}, sync_fails{false};
+std::atomic<bool> malloc_fails{false}, mapping_fails{false}, capturing{false}, sync_fails{false};
 std::string launch_fails; // name of the kernel whose launch fails
 int wait_for = 0, waiting = 0;  // hipStreamSynchronize returns once that many threads are in it
 std::condition_variable all_in;
@@ -59,7 +59,7 @@ hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipSt
     if (!launch_fails.empty() && name.find(launch_fails) != std::string::npos) return error(hipErrorLaunchFailure);
     if (name.find("scan_kernel") != std::string::npos) {
         Totals *host = *static_cast<Totals **>(args[6]);
-        if (host) *host = kTotals;
+        if (host && !capturing) *host = kTotals;
         std::lock_guard<std::mutex> lock(mutex);
         if (host) slots_seen.insert(host);
     }
@@ -86,11 +86,17 @@ hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned)
 hipError_t hipMemcpyAsync(void *to, const void *, size_t bytes, hipMemcpyKind, hipStream_t)
 {
     ++copies;
-    std::memcpy(to, &kTotals, bytes);
+    if (!capturing) std::memcpy(to, &kTotals, bytes);
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *status)
+{
+    *status = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t)
 {
+    if (capturing) return error(hipErrorStreamCaptureUnsupported);
     if (sync_fails) return error(hipErrorLaunchFailure);
     std::unique_lock<std::mutex> lock(mutex);
     ++waiting;
@@ -177,6 +183,16 @@ int main(int argc, char **argv)
             check(rc == ZS_ERR_HIP, (std::string(k) + " not launched, status").c_str(), rc);
             hipGetLastError();
         }
+    } else if (scenario == "capture") { // refused, as every call that waits; no slot is lost by it
+        capturing = true;
+        copies = 0;
+        for (int i = 0; i < 40; ++i) {
+            const int rc = call();
+            check(rc == ZS_ERR_HIP, "under capture, status", rc);
+            hipGetLastError();
+        }
+        capturing = false;
+        calls(3, ZS_OK, 0, "afterwards");
     } else {
         return 2;
     }

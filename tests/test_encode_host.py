@@ -29,7 +29,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["plain", "no_pinned_memory", "no_mapping", "threads", "failed_wait", "failed_launch",
-                                      "failed_launch no_pinned_memory"])
+                                      "failed_launch no_pinned_memory", "capture"])
 def test_packer_host_code(program, scenario):
     done = subprocess.run([str(program)] + scenario.split(), capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stdout + done.stderr
