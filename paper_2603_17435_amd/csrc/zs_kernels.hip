@@ -532,10 +532,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
     ConstArgs in_memory = (ConstArgs)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(StreamKernarg, args));
     asm volatile("" : "+s"(in_memory)); // (not loaded before the offsets are asked for)
     const uint16_t *const A = in_memory->A;
-    float *const C = in_memory->C;
-    const int64_t lda = in_memory->lda, ldc = in_memory->ldc;
-    const int M = in_memory->M;
-    const SharedSums ws = {in_memory->ws.count, in_memory->ws.tiles, in_memory->ws.mode, in_memory->ws.out_bf16, in_memory->ws.tiles_bytes};
+    const int64_t lda = in_memory->lda;
     bv.h_units = in_memory->h_units, bv.l_units = in_memory->l_units;
     bv.h_fast = in_memory->h_fast, bv.l_fast = in_memory->l_fast, bv.base_exp = in_memory->base_exp;
     if (wave < WAVES) stage(0);
@@ -545,7 +542,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
         const uint32_t m = j * 16 + m_lane;
-        rowoff[j] = ((int)m < M ? m : 0u) * (uint32_t)lda * 2u + kgrp * 16u;
+        rowoff[j] = ((int)m < in_memory->M ? m : 0u) * (uint32_t)lda * 2u + kgrp * 16u;
     }
 
     build_tables(smem, bv.base_exp);
@@ -556,7 +553,21 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
 
     // ---- results
     constexpr uint32_t kRows = kUnits / 64;                // rows of 64 float4 units (four tokens each) of a tile
-    const uint32_t rows = min(((uint32_t)M + 3u) / 4u, kRows); // ... that hold tokens
+    // What only results need: loaded where they start (results_begin), so that the streaming loop does not hold it.
+    float *C;
+    int64_t ldc;
+    int M;
+    SharedSums ws;
+    uint32_t rows; // rows that hold tokens
+    __amdgpu_buffer_rsrc_t slots;
+    auto results_begin = [&]() {
+        ConstArgs again = in_memory;
+        asm volatile("" : "+s"(again));
+        C = again->C, ldc = again->ldc, M = again->M;
+        ws = SharedSums{again->ws.count, again->ws.tiles, again->ws.mode, again->ws.out_bf16, again->ws.tiles_bytes};
+        rows = min(((uint32_t)M + 3u) / 4u, kRows);
+        slots = __builtin_amdgcn_make_buffer_rsrc(ws.tiles, 0, (int)ws.tiles_bytes, 0x00020000);
+    };
     auto task_tiles = [&](uint32_t strip) -> uint32_t { return min(g1, (strip + 1) * k_blocks) - max(g0, strip * k_blocks); };
     // [first, last] contributing workgroup of a strip that this range holds only a part of
     auto contributors = [&](uint32_t strip, uint32_t &b_lo, uint32_t &b_hi) {
@@ -612,7 +623,6 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
     // vector instruction overwrites them, except behind a buffer store with a scalar register as offset, where it
     // keeps none.  A word parked by such a store was seen lost; how many that form needs is not known, so it is not used.
     constexpr int kCoherent = 16 | (int)0x80000000u; // sc1 | volatile (compiler-level)
-    const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(ws.tiles, 0, (int)ws.tiles_bytes, 0x00020000);
     auto store_unit = [&](const u32x4 &w, uint32_t at) { __builtin_amdgcn_raw_buffer_store_b128(w, slots, at, 0, kCoherent); };
     // byte offset of the slot of workgroup b for this strip: slot 0 of a workgroup holds
     // the strip its range starts in, slot 1 the one it ends in
@@ -746,6 +756,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
     //      vector-memory counter as the LDS-direct loads, and a store is acknowledged late while
     //      HBM is saturated with reads; a streaming wave that stored would stall its own pipeline.
     if (wave == WAVES) {
+        results_begin();
         for (uint32_t j = 0; j + 1 < n_tasks; ++j) {
             const uint32_t strip = task_strip(j), par = j & 1u, n = task_tiles(strip);
             while (uniform(lds_poll(ctl + kCtlDone + 4 * par)) != n) __builtin_amdgcn_s_sleep(2);
@@ -961,6 +972,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
     }
     // The last task's sums go to the wave's own ring (nothing is read there any more, and the loads
     // of "no tile" have landed), not under a lock: there the waves queued, 1.2 us at 16 tokens and 2.4 at 32.
+    results_begin(); // (arrives while the sums are written)
     wait_dma<0>();
     const uint32_t l = opaque_lane();
 #pragma unroll

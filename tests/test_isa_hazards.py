@@ -311,3 +311,15 @@ def test_no_wide_store_loses_its_data(asm_of):
             found = wide_store_hazards(ins)
             assert not found, f"{source}: {name}: {list(found.values())[:4]}"
     assert len(stores) == 3 and all(stores.values())
+
+
+def test_no_kernel_asks_for_private_memory(asm_of):
+    """A private segment that a kernel declares is set up for its launches whether it is used or not, which a library that
+    promises not to allocate must not ask for."""
+    kernels_seen = 0
+    for source, asm in asm_of.items():
+        for name, size in re.findall(r"\.amdhsa_kernel (\w+)\n(?:.*\n)*?\s*\.amdhsa_private_segment_fixed_size (\d+)", asm):
+            kernels_seen += 1
+            assert int(size) == 0, f"{source}: {name}: {size} bytes"
+        assert not re.search(r"^\s*scratch_(load|store)", asm, re.M), source
+    assert kernels_seen > 40
