@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
-#include <cstddef>
 #include <cstring>
 #include <type_traits>
 
@@ -425,12 +424,18 @@ struct StreamArgs {
     uint32_t h_units, l_units, h_fast, l_fast, magic_q, magic_q1;
 };
 
-// The arguments in memory as the launch lays them out.
-struct StreamKernarg {
-    const void *offsets, *bitmaps, *H, *L;
-    uint32_t q, r, parts, k_blocks, magic_k;
-    StreamArgs args;
-};
+// Where the StreamArgs lie in the memory of the arguments: behind the scalar ones, each at the next multiple of its
+// alignment.  The launch checks that the kernel's arguments are those of StreamKernel.
+using StreamKernel = void (*)(const u32x2 *, const uint8_t *, const uint8_t *, const uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t,
+                              uint32_t, StreamArgs);
+template <class... Args>
+constexpr size_t last_argument_at(void (*)(Args...))
+{
+    size_t end = 0, at = 0;
+    ((at = (end + alignof(Args) - 1) / alignof(Args) * alignof(Args), end = at + sizeof(Args)), ...);
+    return at;
+}
+constexpr size_t kStreamArgsAt = last_argument_at(StreamKernel{});
 
 // The scalar arguments in front, 13 words, arrive in registers with the launch (the build asks for kernel
 // argument preloading): what the offsets of the first BlockTile depend on is there at the first instruction, and
@@ -529,7 +534,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
         take_lookup();
     }
     typedef const StreamArgs __attribute__((address_space(4))) *ConstArgs;
-    ConstArgs in_memory = (ConstArgs)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(StreamKernarg, args));
+    ConstArgs in_memory = (ConstArgs)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + kStreamArgsAt);
     asm volatile("" : "+s"(in_memory)); // (not loaded before the offsets are asked for)
     const uint16_t *const A = in_memory->A;
     const int64_t lda = in_memory->lda;
@@ -1462,6 +1467,7 @@ int launch_gemm(const BlobView &bv, const uint16_t *A, int64_t lda, float *C, in
     auto kern = site == 0   ? gemm_stream_kernel<MT, LW, WAVES, true, kRows>
                 : site == 1 ? gemm_stream_kernel<MT, LW, WAVES, false, kLoop>
                             : gemm_stream_kernel<MT, LW, WAVES, false, kRows>;
+    static_assert(std::is_same_v<decltype(kern), StreamKernel>, "the kernel finds its StreamArgs by the arguments before them");
     int rc = allow_big_lds(kern, lds, device, lds_allowed[site]);
     if (rc != ZS_OK) return rc;
     const RangeSplit rs = split_ranges((uint32_t)bv.strips * (uint32_t)bv.k_blocks, wgs);
