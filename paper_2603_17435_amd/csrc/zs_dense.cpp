@@ -111,8 +111,8 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // On the small ones (under 40 BlockTiles per compute unit) the switch at 128 tokens dates from fused
 // kernels that were up to twice as slow at 65..256 tokens; with the present ones it would pay from
 // 257 at 6144 x 4096 (128 29 / 41, 256 44 / 55), 256 at 4096 x 4096 (128 24 / 37, 224 33 / 34, 256 36 / 34) and
-// 224 at 1024 x 4096 (128 18 / 23, 224 24.0 / 22.6).  It has stayed: zs_linear_path answers it, and programs
-// size their workspace by that.
+// 224 at 1024 x 4096 (128 18 / 23, 224 24.0 / 22.6).  Nothing stands in the way of moving it (the fused kernel for
+// 65..256 tokens uses no workspace); three shapes are too few to draw the new line by.
 int64_t decoupled_from(const zs_desc *d)
 {
     const int64_t tiles_per_cu = (d->N / 64) * (d->K / 64) / zs_compute_units();

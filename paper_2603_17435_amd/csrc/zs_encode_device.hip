@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t *W, int64_t ld
         for (uint32_t c = 0; c < max_units; c += 64) {
             if (c >= units) break;
             const uint32_t u = c + lane;
-            if (u < units && at + 16ull * u + 16 <= cap) // (non-temporal: below)
+            if (u < units && at + 16ull * u + 16 <= cap) // (non-temporal: see above the kernel)
                 __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(from + 16 * u),
                                             reinterpret_cast<u32x4 *>(blob + at + 16ull * u));
         }

@@ -43,8 +43,11 @@ struct Slot {
 
 // LDS image of a gemm_stream_kernel workgroup, shared by the kernel (addresses) and the host
 // (bytes to request): tables | accumulation tiles | control words | WAVES rings of kDepth slots.
-// Where they fit, every streaming wave has an accumulation tile of its own; else there are two, used by turns
-// under a lock.
+// Where they fit (eight waves at 16 tokens, seven at 32), every streaming wave has an accumulation tile of its own;
+// else there are two, used by turns under a lock.  Measured against two tiles there as well (cleared only where a
+// range has more than one task), the line is not clear-cut, us, own / two: 28672 x 1024, 32 tokens 18.3 / 18.7; 32768 x
+// 2048, 16 tokens 23.8 / 24.5; but 3072 x 4096, 16 tokens 13.4 / 12.2; 6144 x 4096, 16 tokens 15.1 / 14.6; 10240 x 4096,
+// 32 tokens 23.1 / 22.0; 14336 x 1024, one token 12.4 / 11.7; of 45 sizes and token counts half differ by less than 1 %.
 template <int MT, int LW, int WAVES>
 struct StreamLds {
     static constexpr uint32_t kDepth = 2; // ring positions per wave: one tile decoded, one in flight
@@ -213,7 +216,7 @@ __device__ __forceinline__ StagedL stage_tile(const BlobView &bv, const TileRef 
 // --------------------------------------------------------------------------------------
 // Standalone decompression: waves take BlockTiles round-robin; 16 bytes (8 weights) per lane
 // and TensorCoreTile are stored row-major, in whole cache lines.  Bound by memory: 28672 x 4096 reads
-// and writes 403 MB in 77.4 us, 5.2 TB/s, the rate of a device copy; with half lines it wrote 265 MB
+// and writes 403 MB in 76.5 us, 5.3 TB/s, the rate of a device copy; with half lines it wrote 265 MB
 // for 235 and took 98.8 us.  4096 x 14336: 37.7 -> 33.8 us.  Without the non-temporal hint 83 and 44 us.
 // LINES = false stores each TensorCoreTile as it is decoded, in half lines (zs_decompress says when).
 // --------------------------------------------------------------------------------------
@@ -238,8 +241,8 @@ __global__ __launch_bounds__(64 * WAVES) void decompress_kernel(BlobView bv, uin
         const bool valid = bt < n_bt;
         stage_tile<LW>(bv, valid ? TileRef{bt, offset_quad(bv, bt)} : TileRef{kNoTileG, kNoTileOff}, ring + j * S::kBytes, lane);
     }
-    // Built behind the first loads, which hide it: 1024 x 4096 7.25 -> 7.0 us, 6144 x 4096 17.4 -> 16.3, 4096 x 14336 40.4 -> 39.7,
-    // 28672 x 4096 77.6 -> 76.9 (one matrix after the other, cold).
+    // Built behind the first loads, which hide it: 1024 x 4096 7.25 -> 7.0 us, 6144 x 4096 17.4 -> 16.3, 4096 x 14336 40.4 -> 39.7
+    // (one matrix after the other, cold); nothing beyond the noise at 28672 x 4096.
     build_tables(smem, bv.base_exp);
     __syncthreads();
     uint32_t cur = 0, nxt = DEPTH - 1; // ring positions of the tile being decoded / being issued
@@ -752,8 +755,10 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(const u32
             request_rows(t, slot_lo, b_lo, q0, l, b_lo, b_hi);
             finish_rows(t, strip, slot_lo, q0, l, b_lo, b_hi);
         };
-        if (MT == 4 || b_hi - b_lo < 4) collect(std::integral_constant<int, 4>{});
-        else collect(std::integral_constant<int, MT == 4 ? 4 : 16 / MT>{});
+        // From five contributors on 16 / MT at a time, us, four always / so: 1024 x 4096, one token 9.0 / 8.2, 32 tokens 11.7 /
+        // 11.3; 1024 x 14336, 16 tokens 13.3 / 12.4, 32 tokens 15.7 / 15.3 (sixteen contributors and more; with two to four no difference).
+        if (16 / MT == 4 || b_hi - b_lo < 4) collect(std::integral_constant<int, 4>{});
+        else collect(std::integral_constant<int, 16 / MT>{});
         if (wave == 0) reset_count(b_lo);
     };
 
@@ -1514,7 +1519,8 @@ int variant_for(const zs_desc *d, int64_t M, int cus)
 {
     // Up to 64 tokens every wave decodes and multiplies for itself; beyond, the decode is shared.  (From 33
     // tokens, FP32 output, p64 / m64: 50 tokens, 6144 x 4096 20.2 / 24.4 us, 1024 x 4096 11.8 / 16.7; but 4096 x 4096, 48 tokens, 16.1 / 15.5;
-    // 64 tokens, 8192 x 4096 23.7 / 21.5, 28672 x 4096 57.3 / 53.3, 4096 x 14336 33.2 / 30.7.)
+    // 64 tokens, 8192 x 4096 23.7 / 21.5, 28672 x 4096 57.3 / 53.3, 4096 x 14336 33.2 / 30.7.  Which is faster goes with the
+    // contributors to a strip and the tasks of a range; no line over them has been drawn.)
     const int lw = pick_l_window(d);
     const int tokens = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
     const bool shared_decode = tokens > 64;
