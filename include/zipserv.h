@@ -12,11 +12,18 @@
  *     (Section 2.1); only the letters differ.
  *   - BF16 values travel as uint16_t bit patterns.
  *   - Every function returns ZS_OK (0) or a negative zs_status; nothing throws.
- *   - The library never allocates or frees device memory and never creates streams:
+ *   - The library's own code never allocates or frees device memory and never creates streams:
  *     the caller owns every buffer and the stream.  "host" / "device" below say where a
- *     pointer must live.  Device entry points are asynchronous on the given stream.
- *   - No global mutable state: calls are thread-safe as long as their output buffers
- *     (and scratch buffers, where one is passed) are distinct.
+ *     pointer must live.  Device entry points are asynchronous on the given stream, except
+ *     zs_encode_device, which waits for it.
+ *   - Calls are thread-safe as long as their output buffers (and scratch buffers, where one is
+ *     passed) are distinct.  What the process keeps between calls: what was asked of a device
+ *     once (its number of compute units, kernel attributes); one page of pinned host memory in
+ *     sixteen slots, allocated by the first zs_encode_device (a call takes a slot and gives it
+ *     back before it returns, one that finds none copies its totals instead, and a slot whose
+ *     call's wait failed stays taken); a hipBLASLt handle per device and a plan per problem
+ *     shape (zs_dense_gemm, zs_linear); the scratch array of zs_gemm_noalloc, whose calls
+ *     must not overlap on one GPU.
  *
  * Blob layout (position independent: offsets only, the same bytes are valid on host
  * and device; the base must be 256-byte aligned).  Geometry, Section 4.2:
