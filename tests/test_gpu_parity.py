@@ -198,7 +198,7 @@ def test_gemm_workgroup_counts(gu):
 @pytest.mark.parametrize("contributors", [2, 4, 5, 6, 7, 8, 9, 10, 17, 18, 40])
 def test_gemm_exchange_batches(gu, contributors, M):
     """One strip summed from several workgroups, around the number of partial tiles that are read at a
-    time (4 and 16); the scratch buffer is zero again afterwards."""
+    time (4; from five on 16, 8 or 4 for up to 16, 32 and 64 tokens); the scratch buffer is zero again afterwards."""
     import torch
     K = 64 * contributors                       # one BlockTile, so one workgroup, per contributor
     W, A = inputs.gaussian_weights(64, K, 70), inputs.activations(M, K, 71 + M)
@@ -422,8 +422,9 @@ def test_encode_device_equals_host_encoder(kind, N, K, pad):
 
 @pytest.mark.parametrize("n_threads", [3, 20])
 def test_encode_device_from_threads(n_threads):
-    """Calls under way at the same time, each on its own thread and stream, get their own totals: fewer than there
-    are slots of pinned memory for them, and more (those beyond copy)."""
+    """Calls under way at the same time, each on its own thread and stream, get their own totals: fewer than there are slots of
+    pinned memory for them, and more.  (Whether more than sixteen meet is up to the threads; that those beyond copy is what
+    tests/test_encode_host.py makes happen.)"""
     import threading
 
     import torch
@@ -432,7 +433,7 @@ def test_encode_device_from_threads(n_threads):
     W = [inputs.make_weights(kinds[t % 3], *shapes[t], seed=200 + t) for t in range(n_threads)]
     w_dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in W]
     torch.cuda.synchronize()
-    got, start = [None] * n_threads, threading.Barrier(n_threads)
+    got, start = [None] * n_threads, threading.Barrier(n_threads, timeout=60)
 
     def work(t):
         N, K = shapes[t]
